@@ -31,6 +31,7 @@
 #include <algorithm>
 #include <vector>
 
+#include "bpe_pairs.hpp"
 #include "common.hpp"
 #include "device.hpp"
 
@@ -134,11 +135,12 @@ int build_bpe_tables(dnatok_vocab *v) {
     DNATOK_HIP(dev_alloc(&p, chars.size()));
     t.d_tok_chars = static_cast<uint8_t *>(p);
     DNATOK_HIP(hipMemcpy(t.d_tok_chars, chars.data(), chars.size(), hipMemcpyHostToDevice));
-    return DNATOK_OK;
+    return build_bpe_chunk_tables(v);
 }
 
 void free_bpe_tables(dnatok_vocab *v) {
     BpeTables &t = v->bpe;
+    if (t.d_chunk) (void)hipFree(t.d_chunk);
     if (t.d_bucket) (void)hipFree(t.d_bucket);
     if (t.d_pair) (void)hipFree(t.d_pair);
     if (t.d_tok_len) (void)hipFree(t.d_tok_len);
@@ -174,27 +176,6 @@ __device__ __forceinline__ uint16_t symbol_of(uint8_t b) {
     case 'n': return 9;
     default: return DNATOK_ID_UNK;
     }
-}
-
-struct RankTab {
-    const uint4 *bucket;
-    const uint32_t *pair;
-    uint32_t nbk;
-};
-
-// Rank of the pair (a, b), or kNoRank. Specials and N never merge.
-__device__ __forceinline__ uint32_t pair_rank(const RankTab &t, uint32_t a, uint32_t b) {
-    if (a < 5 || a == 9 || b < 5 || b == 9) return kNoRank;
-    const uint32_t key = a | (b << 16);
-    uint32_t b1, b2;
-    bpe_buckets(key, t.nbk, &b1, &b2);
-    const uint4 x = t.bucket[b1], y = t.bucket[b2];
-    uint32_t r = kNoRank;
-    r = (x.x == key) ? x.y : r;
-    r = (x.z == key) ? x.w : r;
-    r = (y.x == key) ? y.y : r;
-    r = (y.z == key) ? y.w : r;
-    return r;
 }
 
 // Table layout in LDS: buckets, then 32-bit pairs.
@@ -298,14 +279,6 @@ __global__ __launch_bounds__(NTE) void k_bpe_items(ItemArgs a) {
 }
 
 // ---- 3. wave per item ---------------------------------------------------------------
-
-// Orders this wave's LDS accesses across lanes (a wave's LDS operations
-// execute in order; the fences keep the compiler from moving them).
-__device__ __forceinline__ void wave_sync() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-}
 
 // Minimum of the 64 pair ranks of block b (16-byte LDS reads).
 __device__ __forceinline__ uint32_t block_min(const uint16_t *prk, uint32_t b) {
@@ -1281,7 +1254,7 @@ int64_t bpe_workspace_tiles(int64_t nbytes, int32_t n, int32_t S) {
     const int64_t units_rows = std::max<int64_t>(1, ((int64_t)n + 4095) / 4096);
     const int64_t units_items =
         std::max<int64_t>(1, (bpe_scratch(nbytes, n, S).max_items + kScanUnit - 1) / kScanUnit);
-    return std::max(units_rows, units_items);
+    return std::max({units_rows, units_items, bpe_chunk_tiles(nbytes, n)});
 }
 
 int launch_bpe_encode(const dnatok_vocab *v, const uint8_t *d_bytes, int64_t nbytes, const int64_t *d_offsets,
@@ -1302,6 +1275,9 @@ int launch_bpe_encode(const dnatok_vocab *v, const uint8_t *d_bytes, int64_t nby
     if (rc) return rc;
     rc = ensure_scratch(ws, bs.total);
     if (rc) return rc;
+    bool chunked = false;
+    rc = launch_bpe_chunks(v, d_bytes, nbytes, d_offsets, n, d_ids, cap, d_out_offsets, d_mask, o, ws, stream, &chunked);
+    if (rc || chunked) return rc;
     uint8_t *sp = ws->d_scratch;
     uint16_t *symA = reinterpret_cast<uint16_t *>(sp);
     sp += sz_sym;

@@ -79,6 +79,15 @@ struct BpeTables {
     int32_t *d_tok_len = nullptr;   // decoded length per id, [vocab]
     int64_t *d_tok_off = nullptr;   // offset of each id's bases in d_tok_chars, [vocab]
     uint8_t *d_tok_chars = nullptr;
+    // chunk path (bpe_chunks.hip), where the table allows it
+    bool chunked = false;
+    uint32_t n_states = 0;                 // of the automaton
+    uint32_t rw = 0;                       // words per row of d_compat
+    uint8_t *d_chunk = nullptr;            // all of these; first [n_states][4]: 4 * the successor
+    const uint16_t *d_longest = nullptr;   // [n_states] longest token that starts here
+    const uint2 *d_info = nullptr;         // [vocab] next shorter tokens that begin it, and bases
+    const uint32_t *d_kid = nullptr;       // trie nodes [4]: token | node << 16
+    uint32_t *d_compat = nullptr;          // [vocab][rw] bits: ids that may follow
 };
 
 }  // namespace dnatok
@@ -109,8 +118,17 @@ namespace dnatok {
 // the next one, so no memset is ever enqueued between launches (graph capture
 // friendly). One workspace exists per (device, stream).
 // Words 8..16 hold the BPE length-class queue counters (counts 4, tickets 4,
-// done), zero between launches.
-enum HdrSlot { HDR_TICKET = 0, HDR_DONE = 1, HDR_PARITY = 2, HDR_ERR = 3, HDR_WORDS = 4, HDR_BPE_QUEUES = 8 };
+// done), word 20 the number of BPE chunks that did not meet their neighbour;
+// all zero between launches.
+enum HdrSlot {
+    HDR_TICKET = 0,
+    HDR_DONE = 1,
+    HDR_PARITY = 2,
+    HDR_ERR = 3,
+    HDR_WORDS = 4,
+    HDR_BPE_QUEUES = 8,
+    HDR_BPE_FAILED = 20
+};
 
 struct Workspace {
     int device = 0;
@@ -185,7 +203,8 @@ int launch_encode_multi(const dnatok_vocab *const *vs, int nv, const uint8_t *d_
 
 // Row scan of the closed-form token counts: out[i] = base + the sum over
 // rows r < i of len_r, len = body + 2 * cls with body = L (kmer = 0),
-// ceil(L / k) (frames) or L - k + 1, one for 0 < L < k (overlap). Raises
+// ceil(L / k) (frames; kmer = 2: at least one) or L - k + 1, one for 0 < L < k
+// (overlap). Raises
 // DNATOK_DERR_OFFSETS for bad offsets and, PADDED, DNATOK_DERR_ROW_WIDTH
 // for a row longer than W.
 struct RowScanSpec {
@@ -203,9 +222,10 @@ struct RowScanSpec {
 };
 int launch_rowscan_spec(const RowScanSpec &sp, hipStream_t stream);
 
-// out[i] = sum over rows r < i of ceil(L_r / divisor) + 2 * cls (out[n] = total).
+// out[i] = sum over rows r < i of ceil(L_r / divisor) + 2 * cls (out[n] = total);
+// at_least_one: a row of no bases counts as one frame.
 int launch_rowscan(const int64_t *d_offsets, int32_t n, int64_t nbytes, int64_t *d_out, int32_t divisor, int32_t cls,
-                   hipStream_t stream);
+                   hipStream_t stream, bool at_least_one = false);
 
 // One length class of the wave-per-item BPE kernel.
 struct BpeClass {
@@ -220,6 +240,14 @@ int bpe_wave_classes(uint32_t table_lds_bytes, int max_waves, BpeClass *out, int
 // with nominal item length S.
 int64_t bpe_scratch_bytes(int64_t nbytes, int32_t n, int32_t S);
 int64_t bpe_workspace_tiles(int64_t nbytes, int32_t n, int32_t S);
+
+// The chunk path (bpe_chunks.hip): its tables, the status words it scans
+// with, and the encode itself, which sets *used when it takes the call.
+int build_bpe_chunk_tables(dnatok_vocab *v);
+int64_t bpe_chunk_tiles(int64_t nbytes, int32_t n);
+int launch_bpe_chunks(const dnatok_vocab *v, const uint8_t *d_bytes, int64_t nbytes, const int64_t *d_offsets,
+                      int32_t n, int32_t *d_ids, int64_t cap, int64_t *d_out_offsets, int8_t *d_mask,
+                      const dnatok_encode_opts &o, Workspace *ws, hipStream_t stream, bool *used);
 
 int launch_bpe_encode(const dnatok_vocab *v, const uint8_t *d_bytes, int64_t nbytes, const int64_t *d_offsets,
                       int32_t n, int32_t *d_ids, int64_t cap, int64_t *d_out_offsets, int8_t *d_mask,

@@ -949,14 +949,14 @@ int launch_rowscan_spec(const RowScanSpec &sp, hipStream_t stream) {
 }
 
 int launch_rowscan(const int64_t *d_offsets, int32_t n, int64_t nbytes, int64_t *d_out, int32_t divisor, int32_t cls,
-                   hipStream_t stream) {
+                   hipStream_t stream, bool at_least_one) {
     RowScanSpec sp;
     sp.offs = d_offsets;
     sp.n = n;
     sp.nbytes = nbytes;
     sp.out = d_out;
     sp.k = divisor;
-    sp.kmer = 1;
+    sp.kmer = at_least_one ? 2 : 1;
     sp.overlap = 0;
     sp.cls = cls;
     sp.padded = 0;

@@ -36,7 +36,7 @@ struct RowScanArgs {
     int64_t *out_offs;
     int32_t k;
     uint32_t kinv;  // floor((2^32 - 1) / k)
-    int32_t kmer;
+    int32_t kmer;     // frames of k (2: at least one per row)
     int32_t overlap;  // k-mer windows of stride 1: L - k + 1 (one for 0 < L < k)
     int32_t cls;
     int32_t padded;
@@ -76,6 +76,7 @@ __device__ __forceinline__ int64_t rowscan_unit(const RowScanArgs &a, int64_t ro
             const int64_t L = o1 - o0;
             int64_t nb = L;
             if (a.kmer) nb = a.overlap ? (L >= a.k ? L - a.k + 1 : (L > 0 ? 1 : 0)) : div_k(L + a.k - 1, a.k, a.kinv);
+            if (a.kmer == 2 && nb == 0) nb = 1;
             len[j] = nb + 2 * a.cls;
             if (a.padded && len[j] > a.W) err |= DNATOK_DERR_ROW_WIDTH;
         }
