@@ -462,19 +462,15 @@ int dnatok_ids_map(const int32_t *lut256, int32_t pad_id, const uint8_t *h_bytes
  * every setting.
  */
 typedef struct dnatok_tuning {
-    int32_t tile_bytes;     /* SINGLE/LUT256/KMER: input bytes per tile, power of two 4096..65536 (0 = default) */
-    int32_t blocks_per_cu;  /* SINGLE/LUT256/KMER: workgroups per CU, 0 = as many as fit */
-    int32_t bpe_item_bytes; /* BPE: nominal item length S, power of two 1024..65536 (0 = 8192) */
-    int32_t bpe_max_waves;  /* BPE: most waves per workgroup of the length classes: 1, 2, 4 or 8 (0 = 8) */
-    int32_t spread;         /* SINGLE/LUT256/KMER: 0 = every workgroup walks a static share of the tiles;
-                               1..100 = one tile per workgroup: the first resident round by workgroup
-                               index, the rest from a ticket counter, with this percentage of the tiles
-                               as extra workgroups, so the parts of the chip that finish early take more */
-    int32_t bands;          /* SINGLE/LUT256/KMER, PADDED layout: 0 = default, 1 = row bands (a workgroup
-                               stages the bytes of a few whole rows, or of a part of a longer row, at most
-                               tile_bytes, and writes all their cells), 2 = tiles, 3 = row bands taken by
-                               resident workgroups in turn, the next band's bytes fetched while the current
-                               one is written (a band staging more than 16 KiB less 64 bytes runs as 1) */
+    int32_t tile_bytes;     /* SINGLE/LUT256/KMER: input bytes per workgroup, power of two 4096..65536 (0 =
+                               default; above 32768 as 32768) */
+    int32_t blocks_per_cu;  /* accepted (0..64) and returned; the kernel that read it is gone */
+    int32_t bpe_item_bytes; /* BPE tables with tokens of more than 64 bases: nominal item length S, power of
+                               two 1024..65536 (0 = 8192) */
+    int32_t bpe_max_waves;  /* the same tables: most waves per workgroup of the length classes: 1, 2, 4 or 8
+                               (0 = 8) */
+    int32_t spread;         /* accepted (0..100) and returned, as blocks_per_cu */
+    int32_t bands;          /* accepted (0..3) and returned, as blocks_per_cu */
 } dnatok_tuning;
 
 int dnatok_get_tuning(const dnatok_vocab *v, dnatok_tuning *out);

@@ -466,9 +466,6 @@ int dnatok_encode(const dnatok_vocab *v, const uint8_t *d_bytes, int64_t nbytes,
     if (v->kind == DNATOK_BPE)
         return launch_bpe_encode(v, d_bytes, nbytes, d_offsets, n, d_ids, ids_capacity, d_out_offsets, d_mask, o,
                                  static_cast<hipStream_t>(stream));
-    if (o.variant)
-        return launch_encode_variant(v, d_bytes, nbytes, d_offsets, n, d_ids, ids_capacity, d_out_offsets, d_mask, o,
-                                     static_cast<hipStream_t>(stream));
     return launch_encode(v, d_bytes, nbytes, d_offsets, n, d_ids, ids_capacity, d_out_offsets, d_mask, o,
                          static_cast<hipStream_t>(stream));
 }
@@ -488,9 +485,6 @@ int dnatok_encode_noalloc(const dnatok_vocab *v, const uint8_t *d_bytes, int64_t
     FixedWorkspaceScope scope(ws);
     if (v->kind == DNATOK_BPE)
         return launch_bpe_encode(v, d_bytes, nbytes, d_offsets, n, d_ids, ids_capacity, d_out_offsets, d_mask, o, s);
-    if (o.variant)
-        return launch_encode_variant(v, d_bytes, nbytes, d_offsets, n, d_ids, ids_capacity, d_out_offsets, d_mask, o,
-                                     s);
     return launch_encode(v, d_bytes, nbytes, d_offsets, n, d_ids, ids_capacity, d_out_offsets, d_mask, o, s);
 }
 

@@ -2,6 +2,7 @@
 #pragma once
 
 #include "common.hpp"
+#include "device.hpp"
 
 namespace dnatok {
 
@@ -28,13 +29,7 @@ __device__ __forceinline__ uint32_t pair_rank(const RankTab &t, uint32_t a, uint
     return r;
 }
 
-// Orders this wave's LDS accesses across lanes (a wave's LDS operations
-// execute in order; the fences keep the compiler from moving them).
-__device__ __forceinline__ void wave_sync() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-}
+using dev::wave_sync;
 
 }  // namespace
 

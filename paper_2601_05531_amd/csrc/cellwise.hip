@@ -1,6 +1,5 @@
-// Output-parallel cell kernel: encode variants (reverse complement,
-// overlapping k-mers) and the embedding lookup, fused with the encode or
-// applied to given identifiers.
+// Output-parallel cell kernel: the embedding lookup, fused with the encode
+// (every variant) or applied to given identifiers.
 //
 // Paper: Design (the embedder embed_tokens maps B x T identifiers to
 // B x T x D activations; the bytes branch of the EmbedFromStrings algorithm
@@ -9,10 +8,9 @@
 // Augmentation" (reverse complement as a character-level map suited to the
 // GPU); Introduction (overlapping k-mers of stride 1, L - k + 1 tokens).
 //
-// MI355X-first decomposition. In these forms the output dominates the
-// traffic: an embedding row of D values per token (256 bytes for D = 128 in
-// bf16, against about one input byte), or one id per base for stride-1
-// windows. Work is therefore cut by output cells rather than input tiles:
+// MI355X-first decomposition. The output dominates the traffic: an embedding
+// row of D values per token (256 bytes for D = 128 in bf16, against about one
+// input byte). Work is therefore cut by output cells rather than input tiles:
 //  * A block takes chunks of NT * CPT consecutive cells (cells = tokens plus
 //    pads); each thread takes CPT consecutive cells of the chunk, so its ids
 //    go out as one 16-byte store and its mask bytes as one word. The thread
@@ -23,11 +21,11 @@
 //    every cell first (pad, CLS, SEP or body token, and the bytes a body
 //    token reads), then issues all of its reads at once: a k-mer reads the
 //    three (k <= 8) or five dwords that hold it and classifies them with
-//    the same 16-byte classifier the tile kernel uses; reverse complement
+//    the same 16-byte classifier the encode uses; reverse complement
 //    reverses and complements the digits in registers (the bytes are never
 //    rewritten), and for table kinds it reads a table already mapped
 //    through the complement.
-//  * With an embedding table the chunk's ids go to LDS and the block copies
+//  * The chunk's ids go to LDS and the block copies
 //    the table rows out in UB-byte units (UB = 16 whenever the row size and
 //    pointers allow): lane l of a wave moves unit l, so a wave writes 1 KiB
 //    of contiguous output per instruction. Several units are loaded before
@@ -52,7 +50,7 @@ constexpr int CPT = 4;                       // cells per thread per chunk (a mu
 constexpr int64_t kChunk = (int64_t)NT * CPT;
 constexpr int kCopyUnroll = 4;               // table units loaded before they are stored
 
-enum CwMode { CW_ENCODE = 0, CW_EMBED = 1, CW_GATHER = 2 };
+enum CwMode { CW_EMBED = 1, CW_GATHER = 2 };
 
 struct CwArgs {
     const uint8_t *bytes;
@@ -453,36 +451,32 @@ __global__ __launch_bounds__(NT) void k_cellwise(CwArgs a) {
                 }
             }
         }
-        if (MODE != CW_ENCODE) {
 #pragma unroll
-            for (int i = 0; i < CPT; ++i) s_id[tid * CPT + i] = id[i];
-            typedef typename Unit<UB>::T V;
-            __syncthreads();
-            const uint32_t units = (uint32_t)(cend - c0) * a.ru;
-            uint8_t *ob = a.emb + c0 * a.row_bytes;
-            for (uint32_t u0 = tid; u0 < units; u0 += NT * kCopyUnroll) {
-                V v[kCopyUnroll];
-                uint32_t cell[kCopyUnroll], part[kCopyUnroll];
+        for (int i = 0; i < CPT; ++i) s_id[tid * CPT + i] = id[i];
+        typedef typename Unit<UB>::T V;
+        __syncthreads();
+        const uint32_t units = (uint32_t)(cend - c0) * a.ru;
+        uint8_t *ob = a.emb + c0 * a.row_bytes;
+        for (uint32_t u0 = tid; u0 < units; u0 += NT * kCopyUnroll) {
+            V v[kCopyUnroll];
+            uint32_t cell[kCopyUnroll], part[kCopyUnroll];
 #pragma unroll
-                for (int t = 0; t < kCopyUnroll; ++t) {
-                    const uint32_t u = u0 + t * NT;
-                    cell[t] = udiv(u, a.ru, a.ruinv);
-                    part[t] = u - cell[t] * a.ru;
-                    const int32_t rid = u < units ? s_id[cell[t]] : -1;
-                    if (rid >= 0) v[t] = *reinterpret_cast<const V *>(a.table + (int64_t)rid * a.row_bytes + part[t] * UB);
-                    else v[t] = V{};
-                }
-#pragma unroll
-                for (int t = 0; t < kCopyUnroll; ++t) {
-                    const uint32_t u = u0 + t * NT;
-                    if (u < units)
-                        __builtin_nontemporal_store(v[t], reinterpret_cast<V *>(ob + (int64_t)cell[t] * a.row_bytes + part[t] * UB));
-                }
+            for (int t = 0; t < kCopyUnroll; ++t) {
+                const uint32_t u = u0 + t * NT;
+                cell[t] = udiv(u, a.ru, a.ruinv);
+                part[t] = u - cell[t] * a.ru;
+                const int32_t rid = u < units ? s_id[cell[t]] : -1;
+                if (rid >= 0) v[t] = *reinterpret_cast<const V *>(a.table + (int64_t)rid * a.row_bytes + part[t] * UB);
+                else v[t] = V{};
             }
-            __syncthreads();
-        } else if (!a.padded) {
-            __syncthreads();  // s_rows is rewritten for the next chunk
+#pragma unroll
+            for (int t = 0; t < kCopyUnroll; ++t) {
+                const uint32_t u = u0 + t * NT;
+                if (u < units)
+                    __builtin_nontemporal_store(v[t], reinterpret_cast<V *>(ob + (int64_t)cell[t] * a.row_bytes + part[t] * UB));
+            }
         }
+        __syncthreads();
     }
     if (err) dev::raise_error(a.err_hdr, err);
 }
@@ -599,27 +593,6 @@ int setup_encode(CwArgs &a, const dnatok_vocab *v, const uint8_t *d_bytes, int64
 }
 
 }  // namespace
-
-int launch_encode_variant(const dnatok_vocab *v, const uint8_t *d_bytes, int64_t nbytes, const int64_t *d_offsets,
-                          int32_t n, int32_t *d_ids, int64_t cap, int64_t *d_out_offsets, int8_t *d_mask,
-                          const dnatok_encode_opts &o, hipStream_t stream) {
-    const EncodeTuning tune = encode_tuning(v, nbytes);
-    if (o.layout == DNATOK_PADDED && (tune.bands == 1 || tune.bands == 3)) {
-        bool used = false;
-        int rc = launch_encode_bands(&v, 1, d_bytes, nbytes, d_offsets, n, &d_ids, &cap, &d_mask, &o,
-                                     tune.tile_bytes, tune.bands == 3, &d_out_offsets, stream, &used);
-        if (rc || used) return rc;
-    }
-    CwArgs a;
-    int64_t max_cells = 0;
-    int rc = setup_encode(a, v, d_bytes, nbytes, d_offsets, n, d_out_offsets, o, stream, &max_cells);
-    if (rc) return rc;
-    a.ids = d_ids;
-    a.mask = a.padded ? d_mask : nullptr;
-    a.cap = cap;
-    if (max_cells < 0 || max_cells > cap) max_cells = cap;
-    return launch_cw_k<CW_ENCODE, 16>(a, max_cells, stream);
-}
 
 int launch_embed(const dnatok_vocab *v, const uint8_t *d_bytes, int64_t nbytes, const int64_t *d_offsets, int32_t n,
                  const void *d_table, int64_t n_rows, int64_t row_bytes, void *d_out, int64_t out_rows,

@@ -94,7 +94,8 @@ struct BpeTables {
 
 struct dnatok_vocab {
     // Scheduling knobs (dnatok_set_tuning / dnatok_autotune); 0 = default.
-    // They change how work is tiled, never the ids.
+    // They change how work is tiled, never the ids; blocks, spread and bands
+    // are kept and returned but no kernel reads them any more.
     std::atomic<int32_t> tune_tile{0}, tune_blocks{0}, tune_item{0}, tune_waves{0}, tune_spread{0}, tune_bands{0};
     int32_t kind = 0;
     int32_t k = 1;
@@ -171,13 +172,7 @@ int device_cu_count();
 
 // ---- launchers (encode.hip / decode.hip / bpe.hip) ------------------------------
 
-struct EncodeTuning {
-    int64_t tile_bytes;  // bytes of input per tile (multiple of 16)
-    int blocks_per_cu;   // 0 = as many as occupancy allows
-    int spread;          // 0 = static walkers; > 0: ticketed tiles plus this percentage of extra workgroups
-    int bands;           // PADDED: 0 = default, 1 = row bands, 2 = tiles, 3 = persistent row bands
-};
-EncodeTuning encode_tuning(const dnatok_vocab *v, int64_t nbytes);
+int64_t encode_tile_bytes(const dnatok_vocab *v, int64_t nbytes, int nv, int32_t variant);
 constexpr int32_t kBpeItemBytesDefault = 8192;  // nominal BPE item length S
 constexpr int32_t kBpeItemBytesMin = 1024;
 
@@ -188,13 +183,11 @@ int launch_encode(const dnatok_vocab *v, const uint8_t *d_bytes, int64_t nbytes,
 // One pass over the input writing the same batch for several vocabularies of
 // one kind (SINGLE/LUT256: one; KMER: up to 8, any k), options alike but for
 // pad_to and offset_base.
-// PADDED encode by row bands (bands.hip). Launches and sets *used when the
-// batch suits bands (every row pad_to admits fits stage_bytes), else leaves
-// *used false and launches nothing.
-int launch_encode_bands(const dnatok_vocab *const *vs, int nv, const uint8_t *d_bytes, int64_t nbytes,
-                        const int64_t *d_offsets, int32_t n, int32_t *const *d_ids, const int64_t *caps,
-                        int8_t *const *d_masks, const dnatok_encode_opts *os, int64_t stage_bytes, bool persistent,
-                        int64_t *const *d_out_offsets, hipStream_t stream, bool *used);
+// Encode by wave tiles (rows.hip): every layout, kind but BPE, and variant.
+int launch_encode_rows(const dnatok_vocab *const *vs, int nv, const uint8_t *d_bytes, int64_t nbytes,
+                       const int64_t *d_offsets, int32_t n, int32_t *const *d_ids, const int64_t *caps,
+                       int64_t *const *d_out_offsets, int8_t *const *d_masks, const dnatok_encode_opts *os,
+                       int64_t tile_bytes, hipStream_t stream);
 
 int launch_encode_multi(const dnatok_vocab *const *vs, int nv, const uint8_t *d_bytes, int64_t nbytes,
                         const int64_t *d_offsets, int32_t n, int32_t *const *d_ids, const int64_t *caps,
@@ -253,12 +246,8 @@ int launch_bpe_encode(const dnatok_vocab *v, const uint8_t *d_bytes, int64_t nby
                       int32_t n, int32_t *d_ids, int64_t cap, int64_t *d_out_offsets, int8_t *d_mask,
                       const dnatok_encode_opts &o, hipStream_t stream);
 
-// Output-parallel kernels (cellwise.hip): encode variants (reverse
-// complement, overlapping k-mers), the fused encode + embedding lookup, and
-// the lookup of given ids.
-int launch_encode_variant(const dnatok_vocab *v, const uint8_t *d_bytes, int64_t nbytes, const int64_t *d_offsets,
-                          int32_t n, int32_t *d_ids, int64_t cap, int64_t *d_out_offsets, int8_t *d_mask,
-                          const dnatok_encode_opts &o, hipStream_t stream);
+// Output-parallel kernels (cellwise.hip): the fused encode + embedding
+// lookup, and the lookup of given ids.
 int launch_embed(const dnatok_vocab *v, const uint8_t *d_bytes, int64_t nbytes, const int64_t *d_offsets, int32_t n,
                  const void *d_table, int64_t n_rows, int64_t row_bytes, void *d_out, int64_t out_rows,
                  int64_t *d_out_offsets, int32_t *d_ids, int8_t *d_mask, const dnatok_encode_opts &o,

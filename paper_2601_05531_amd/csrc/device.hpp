@@ -155,6 +155,25 @@ __device__ __forceinline__ void classify16(uint4 v, uint32_t &code, uint32_t &va
     }
 }
 
+// The 16 bytes at base + q0 (16-byte aligned), those outside [lo, hi) as
+// zeros. A 16-byte unit that holds one byte of the input lies in that byte's
+// page, so it is read whole and masked: byte by byte the ends of the input
+// took 16 dependent loads, about 4 us at the end of every launch.
+__device__ __forceinline__ uint4 load16(const uint8_t *base, int64_t q0, int64_t lo, int64_t hi) {
+    lo -= q0;
+    hi -= q0;
+    if (hi <= 0 || lo >= 16 || hi <= lo) return make_uint4(0, 0, 0, 0);
+    const uint4 x = *reinterpret_cast<const uint4 *>(base + q0);
+    uint32_t w[4] = {x.x, x.y, x.z, x.w};
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int32_t f = (int32_t)max(min(lo - 4 * i, (int64_t)4), (int64_t)0);
+        const int32_t e = (int32_t)max(min(hi - 4 * i, (int64_t)4), (int64_t)0);
+        w[i] &= (e >= 4 ? ~0u : (1u << (8 * e)) - 1u) & ~(f >= 4 ? ~0u : (1u << (8 * f)) - 1u);
+    }
+    return make_uint4(w[0], w[1], w[2], w[3]);
+}
+
 // First index in [lo, hi) where the monotone predicate (false...true) holds,
 // or hi, found by one wave: 64 probes per round, so 2 rounds cover 4096
 // candidates and 3 rounds 262144. All 64 lanes must call it.
@@ -262,6 +281,14 @@ __device__ __forceinline__ void finish_block(uint32_t *hdr, bool flip = true) {
         st_relaxed32(hdr + 1, 0u);
         if (flip) st_relaxed32(hdr + 2, ld_relaxed32(hdr + 2) ^ 1u);
     }
+}
+
+// Orders this wave's LDS accesses across lanes (a wave's LDS operations
+// execute in order; the fences keep the compiler from moving them).
+__device__ __forceinline__ void wave_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
 }
 
 }  // namespace dev

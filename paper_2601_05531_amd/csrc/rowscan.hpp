@@ -1,5 +1,5 @@
-// Row scan of the closed-form token counts (shared by the tile kernel, the
-// cell kernel and the stand-alone scan launch): each row's length is L, its
+// Row scan of the closed-form token counts (shared by the encode, the
+// embedding lookup and the stand-alone scan launches): each row's length is L, its
 // number of k-frames ceil(L / k), or its number of stride-1 windows, plus
 // the specials; out_offsets is their exclusive scan. Offsets are validated
 // and clamped here, so every kernel that places cells from them agrees.
@@ -92,6 +92,86 @@ __device__ __forceinline__ int64_t rowscan_unit(const RowScanArgs &a, int64_t ro
         run += len[j];
     }
     return total;
+}
+
+// Length in tokens of a row, and the flags its offsets raise.
+struct RowLen {
+    const int64_t *offs;
+    int64_t nbytes;
+    int32_t n;
+    int32_t k;
+    uint32_t kinv;
+    int32_t kmer, overlap, cls;
+    int64_t W;  // PADDED: the widest row (INT64_MAX otherwise)
+    __device__ __forceinline__ int64_t of(int64_t o0, int64_t o1, uint32_t &err) const {
+        if (o0 < 0 || o1 < o0 || o1 > nbytes) err |= DNATOK_DERR_OFFSETS;
+        o0 = o0 < 0 ? 0 : (o0 > nbytes ? nbytes : o0);
+        o1 = o1 < o0 ? o0 : (o1 > nbytes ? nbytes : o1);
+        const int64_t L = o1 - o0;
+        int64_t nb = L;
+        if (kmer) nb = overlap ? (L >= k ? L - k + 1 : (L > 0 ? 1 : 0)) : div_k(L + k - 1, k, kinv);
+        if (kmer == 2 && nb == 0) nb = 1;
+        const int64_t l = nb + 2 * cls;
+        if (l > W) err |= DNATOK_DERR_ROW_WIDTH;
+        return l;
+    }
+    __device__ __forceinline__ int64_t len(int64_t i, uint32_t &err) const { return of(offs[i], offs[i + 1], err); }
+};
+
+// Offsets of the kScanRows rows of one unit by one workgroup that no other
+// waits for: it adds up the rows before the unit itself (eight in flight per
+// thread) instead of taking the sum over from its predecessors. A batch of a
+// few thousand rows is bound by the latency of its dependent steps, and this
+// form has three (offsets, block scan, stores): 3,001 rows take 5.4 us,
+// where the chained units with their ticket and look-back took 10.4. The
+// reads grow with the square of the rows (8 MB at 65,536), so longer batches
+// keep the chained form.
+constexpr int kScanRows = 1024;
+constexpr int kScanRowsPerThread = kScanRows / kScanNT;
+constexpr int32_t kIndependentMaxRows = 65536;
+[[maybe_unused]] __host__ __device__ inline int64_t rowscan_units(int64_t n) {
+    return n > 0 ? (n + kScanRows - 1) / kScanRows : 1;
+}
+[[maybe_unused]] __device__ __forceinline__ void rowscan_independent(const RowLen &rl, int64_t *out, int64_t base,
+                                                                     int64_t unit, int64_t *s_tmp, uint32_t *err_hdr) {
+    const int tid = threadIdx.x;
+    const int64_t row0 = unit * kScanRows, n = rl.n;
+    uint32_t err = 0, ignore = 0;  // each unit reports its own rows
+    // this unit's offsets and the rows before it are asked for together
+    int64_t off[kScanRowsPerThread + 1];
+    const int64_t i0 = row0 + (int64_t)tid * kScanRowsPerThread;
+#pragma unroll
+    for (int j = 0; j <= kScanRowsPerThread; ++j) off[j] = rl.offs[min(i0 + j, n)];
+    int64_t before = 0;
+    for (int64_t r = tid; r < row0; r += 8 * kScanNT) {
+        int64_t x[8], y[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            const int64_t i = min(r + u * kScanNT, row0 - 1);
+            x[u] = rl.offs[i];
+            y[u] = rl.offs[i + 1];
+        }
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+            if (r + u * kScanNT < row0) before += rl.of(x[u], y[u], ignore);
+    }
+    int64_t len[kScanRowsPerThread], mine = 0;
+#pragma unroll
+    for (int j = 0; j < kScanRowsPerThread; ++j) {
+        len[j] = i0 + j < n ? rl.of(off[j], off[j + 1], err) : 0;
+        mine += len[j];
+    }
+    int64_t total;
+    int64_t run = base + dev::block_excl_scan<kScanNT>(mine, s_tmp, &total);
+    if (row0 > 0) run += dev::block_sum<kScanNT>(before, s_tmp);
+#pragma unroll
+    for (int j = 0; j < kScanRowsPerThread; ++j) {
+        if (i0 + j < n) out[i0 + j] = run;
+        run += len[j];
+        // the last row's owner (or, without rows, the first thread) ends the offsets
+        if (i0 + j == n - 1 || (n == 0 && tid == 0 && j == 0)) out[n] = run;
+    }
+    if (err) dev::raise_error(err_hdr, err);
 }
 
 // Whole batch by one block, units in order (the fused PADDED case).

@@ -81,7 +81,7 @@ namespace {
 // Times every candidate tiling of v with `run` (one encode on `st`): one
 // warm-up sample and `reps` timed samples of 4 launches each, median; keeps the fastest in v.
 template <class Run>
-int autotune_loop(dnatok_vocab *v, hipStream_t st, int32_t reps, bool padded, Run run, dnatok_tuning *best,
+int autotune_loop(dnatok_vocab *v, hipStream_t st, int32_t reps, Run run, dnatok_tuning *best,
                   float *best_ms) {
     if (!v) return set_error(DNATOK_EINVAL, "null vocabulary");
     if (reps < 1 || reps > 100) return set_error(DNATOK_EINVAL, "reps must be 1..100");
@@ -89,19 +89,13 @@ int autotune_loop(dnatok_vocab *v, hipStream_t st, int32_t reps, bool padded, Ru
     if (hipStreamIsCapturing(st, &cs) == hipSuccess && cs != hipStreamCaptureStatusNone)
         return set_error(DNATOK_ESTATE, "autotune cannot run during graph capture");
     std::vector<dnatok_tuning> cand;
-    if (v->kind == DNATOK_BPE) {
+    if (v->kind == DNATOK_BPE && !v->bpe.chunked) {
         for (int32_t S : {2048, 4096, 8192, 16384, 32768})
             for (int32_t w : {8, 4, 2, 1}) cand.push_back(dnatok_tuning{0, 0, S, w, 0, 0});
+    } else if (v->kind == DNATOK_BPE) {
+        cand.push_back(dnatok_tuning{0, 0, kBpeItemBytesDefault, 8, 0, 0});  // the chunk path has no knob
     } else {
-        for (int32_t tile : {4096, 8192, 16384, 32768, 65536})
-            for (int32_t b : {0, 1, 2, 4}) cand.push_back(dnatok_tuning{tile, b, 0, 0, 0, 0});
-        for (int32_t tile : {4096, 8192, 16384})
-            for (int32_t sp : {10, 25, 50}) cand.push_back(dnatok_tuning{tile, 0, 0, 0, sp, 0});
-        if (padded) {  // row bands, staged through LDS stages of 4 to 64 KiB; persistent ones of 4 and 8 KiB
-            // (a 16 KiB persistent stage holds no band of 16 KiB, so it would run as row bands)
-            for (int32_t tile : {4096, 8192, 16384, 32768, 65536}) cand.push_back(dnatok_tuning{tile, 0, 0, 0, 0, 1});
-            for (int32_t tile : {4096, 8192}) cand.push_back(dnatok_tuning{tile, 0, 0, 0, 0, 3});
-        }
+        for (int32_t tile : {4096, 8192, 16384, 32768}) cand.push_back(dnatok_tuning{tile, 0, 0, 0, 0, 0});
     }
     const dnatok_tuning saved = load(v);
     hipEvent_t e0 = nullptr, e1 = nullptr;
@@ -188,8 +182,7 @@ int dnatok_autotune(dnatok_vocab *v, const uint8_t *d_bytes, int64_t nbytes, con
                     int32_t *d_ids, int64_t ids_capacity, int64_t *d_out_offsets, int8_t *d_mask,
                     const dnatok_encode_opts *opts, void *stream, int32_t reps, dnatok_tuning *best,
                     float *best_ms) {
-    const bool padded = opts && opts->layout == DNATOK_PADDED;
-    return autotune_loop(v, static_cast<hipStream_t>(stream), reps, padded, [&] {
+    return autotune_loop(v, static_cast<hipStream_t>(stream), reps, [&] {
         return dnatok_encode(v, d_bytes, nbytes, d_offsets, n, d_ids, ids_capacity, d_out_offsets, d_mask, opts,
                              stream);
     }, best, best_ms);
@@ -200,8 +193,7 @@ int dnatok_autotune_multi(dnatok_vocab *const *vocabs, int32_t n_vocabs, const u
                           int64_t *const *d_out_offsets, int8_t *const *d_mask, const dnatok_encode_opts *opts,
                           void *stream, int32_t reps, dnatok_tuning *best, float *best_ms) {
     if (!vocabs || n_vocabs < 1) return set_error(DNATOK_EINVAL, "no vocabularies");
-    const bool padded = opts && opts[0].layout == DNATOK_PADDED;
-    return autotune_loop(vocabs[0], static_cast<hipStream_t>(stream), reps, padded, [&] {
+    return autotune_loop(vocabs[0], static_cast<hipStream_t>(stream), reps, [&] {
         return dnatok_encode_multi(vocabs, n_vocabs, d_bytes, nbytes, d_offsets, n, d_ids, ids_capacity,
                                    d_out_offsets, d_mask, opts, stream);
     }, best, best_ms);
