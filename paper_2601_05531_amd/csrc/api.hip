@@ -149,9 +149,10 @@ int get_workspace(hipStream_t stream, int64_t tiles, Workspace **out) {
             DNATOK_HIP(hipFree(ws->d_hdr));
             ws->d_hdr = nullptr;
             ws->d_status = nullptr;
+            ws->d_decode = nullptr;
             ws->cap = 0;
         }
-        size_t bytes = 256 + (size_t)cap * 2 * sizeof(uint64_t);
+        size_t bytes = 256 + ((size_t)cap * 2 + kDecodeWords) * sizeof(uint64_t);
         void *p = nullptr;
         DNATOK_HIP(dev_alloc(&p, bytes));
         // zero on the workspace's own stream and wait: a plain hipMemset runs on
@@ -160,6 +161,7 @@ int get_workspace(hipStream_t stream, int64_t tiles, Workspace **out) {
         DNATOK_HIP(hipStreamSynchronize(stream));
         ws->d_hdr = static_cast<uint32_t *>(p);
         ws->d_status = reinterpret_cast<uint64_t *>(static_cast<uint8_t *>(p) + 256);
+        ws->d_decode = ws->d_status + 2 * cap;
         ws->cap = cap;
         ws->high_water = 0;
         if (err_keep) {

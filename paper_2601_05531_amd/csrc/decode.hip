@@ -2,18 +2,20 @@
 // future work, Discussion, "Decode Operations": the same LUT principle run
 // backwards). Not on the hot path.
 //
-// Tiles of TT token positions, each tile's output bytes contiguous. Two
-// launches: a row pass (each tile's first row, the offsets check, and the
-// tile status words cleared), then one workgroup per tile that reads its
-// ids once, sums its output bytes, takes its output position by a
-// decoupled look-back over the tiles before it (Merrill and Garland's
-// single-pass prefix scan), stages its bytes in LDS at their 16-byte phase
-// in the output and writes them with 16-byte stores. Tiles follow the
-// workgroup index: a workgroup starts only after every lower-indexed one
-// on its XCD, and the XCDs take workgroups in index order, so the tile
-// with the lowest index still running never waits and the look-back ends
-// (with no ticket counter: one device-wide counter serializes at about
-// 12 ns per ticket, which at thousands of tiles outweighs the decode).
+// Tiles of token positions, each tile's output bytes contiguous, one
+// workgroup per tile: it reads its ids once, sums its output bytes, takes its
+// output position from the tiles before it, stages its bytes in LDS and
+// writes them with 16-byte stores. Tiles follow the workgroup index: a
+// workgroup starts only after every lower-indexed one on its XCD, and the
+// XCDs take workgroups in index order, so the tile with the lowest index
+// still running never waits and every wait ends (with no ticket counter: one
+// device-wide counter serializes at about 12 ns per ticket, which at
+// thousands of tiles outweighs the decode).
+//
+// Single-nucleotide and k-mer ids (K bytes or none each) take one launch
+// (k_decode_fixed). BPE ids (tokens of any length) take two: a row pass, then
+// the tiles with a decoupled look-back (Merrill and Garland's single-pass
+// prefix scan).
 #include "common.hpp"
 #include "device.hpp"
 
@@ -22,11 +24,11 @@ namespace dnatok {
 namespace {
 
 constexpr int NT = 256;
-constexpr int TPT = 16;  // tokens per thread (fewer, smaller tiles measured slower for every kind)
+constexpr int TPT = 16;  // BPE tokens per thread (fewer, smaller tiles measured slower)
 constexpr int TT = NT * TPT;
-constexpr int kMaxStage = 32768;
-constexpr int TPT_SINGLE = 32;  // single-nucleotide ids per thread in the strided kernel
-constexpr int TT_SINGLE = NT * TPT_SINGLE;  // most bytes of one tile's output staged in LDS
+constexpr int kMaxStage = 32768;  // most bytes of one tile's output staged in LDS
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef int32_t ids4 __attribute__((ext_vector_type(4), aligned(4)));
 
 struct DecodeArgs {
     const int32_t *ids;
@@ -43,25 +45,23 @@ struct DecodeArgs {
     const int64_t *tok_off;
     const uint8_t *tok_chars;
     int64_t ntiles;
-    int64_t tt;          // token positions per tile (TT, or TT_SINGLE for the strided single-nucleotide kernel)
     int32_t stage;       // bytes the LDS stage holds (a tile with more output writes its tokens directly)
-    uint64_t *status;    // tile status words of the look-back (ntiles), cleared by the row pass
-    int64_t *first_row;  // first row starting at or after each tile's first position (ntiles + 1)
+    uint64_t *status;    // BPE: tile status words of the look-back (ntiles), cleared by the row pass
+    int64_t *first_row;  // BPE: first row starting at or after each tile's first position (ntiles + 1)
     uint32_t *err_hdr;
+    // fixed widths
+    double rows_per_id;
+    uint32_t codes;         // 4^k
 };
 
 __device__ __forceinline__ bool is_silent(int32_t id) {
     return id == DNATOK_ID_PAD || id == DNATOK_ID_CLS || id == DNATOK_ID_SEP || id == DNATOK_ID_MASK;
 }
 
-// Output bytes of one id. KIND is the vocabulary kind (a template
-// parameter, so each kind's kernel holds only its own branch).
-template <int KIND>
+// Output bytes of one BPE id.
 __device__ __forceinline__ int32_t width_of(const DecodeArgs &a, int32_t id) {
     if (is_silent(id)) return 0;
-    if (KIND == DNATOK_KMER) return a.k;
-    if (KIND == DNATOK_BPE && id >= 10 && id < a.vocab) return a.tok_len[id];
-    return 1;
+    return id >= 10 && id < a.vocab ? a.tok_len[id] : 1;
 }
 
 // The letter of 2-bit code c (0..3: A, C, G, T) from one packed word: a
@@ -73,22 +73,9 @@ __device__ __forceinline__ uint8_t single_letter(int32_t id) {
     return (id >= 5 && id <= 8) ? base_letter((uint32_t)(id - 5)) : (uint8_t)'N';
 }
 
-template <int KIND>
 __device__ __forceinline__ void write_token(const DecodeArgs &a, int32_t id, int64_t pos, uint32_t &err) {
     if (is_silent(id)) return;
-    if (KIND == DNATOK_KMER) {
-        const bool known = id >= 5 && id < a.vocab;
-        uint32_t v = known ? (uint32_t)(id - 5) : 0u;
-#pragma unroll 1
-        for (int j = a.k - 1; j >= 0; --j) {
-            int64_t p = pos + j;
-            if (p < a.cap) a.out[p] = known ? base_letter(v) : (uint8_t)'N';
-            else err |= DNATOK_DERR_CAPACITY;
-            v >>= 2;
-        }
-        return;
-    }
-    if (KIND == DNATOK_BPE && id >= 10 && id < a.vocab) {
+    if (id >= 10 && id < a.vocab) {
         const int64_t L = a.tok_len[id], o = a.tok_off[id];
 #pragma unroll 1
         for (int64_t j = 0; j < L; ++j) {
@@ -103,20 +90,9 @@ __device__ __forceinline__ void write_token(const DecodeArgs &a, int32_t id, int
 
 // The bytes of one id written to LDS at p (no bounds: the tile's staged
 // output fits the stage).
-template <int KIND>
 __device__ __forceinline__ void stage_token(const DecodeArgs &a, int32_t id, uint8_t *p) {
     if (is_silent(id)) return;
-    if (KIND == DNATOK_KMER) {
-        // digit j (most significant first) is the letter at p[j]; unknown
-        // ids decode to k letters N (0x4E in every byte)
-        const bool known = id >= 5 && id < a.vocab;
-        const uint32_t v = (uint32_t)(id - 5);
-#pragma unroll 1
-        for (int j = 0; j < a.k; ++j)
-            p[j] = known ? base_letter(v >> (2 * (a.k - 1 - j))) : (uint8_t)'N';
-        return;
-    }
-    if (KIND == DNATOK_BPE && id >= 10 && id < a.vocab) {
+    if (id >= 10 && id < a.vocab) {
         const int64_t L = a.tok_len[id], o = a.tok_off[id];
 #pragma unroll 1
         for (int64_t j = 0; j < L; ++j) p[j] = a.tok_chars[o + j];
@@ -125,30 +101,11 @@ __device__ __forceinline__ void stage_token(const DecodeArgs &a, int32_t id, uin
     p[0] = single_letter(id);
 }
 
-// A thread's k-mer tokens to the stage from p on, k fixed at compile time
-// (digit shifts and store offsets become constants: the runtime-k loop cost
-// a dozen instructions per byte and, with every workgroup resident at once,
-// made the staging VALU-bound).
-template <int K>
-__device__ __forceinline__ void stage_kmers(const DecodeArgs &a, const int32_t (&idv)[TPT], uint8_t *p) {
-#pragma unroll
-    for (int j = 0; j < TPT; ++j) {
-        const int32_t id = idv[j];
-        if (is_silent(id)) continue;
-        const bool known = id >= 5 && id < a.vocab;
-        const uint32_t v = (uint32_t)(id - 5);
-#pragma unroll
-        for (int q = 0; q < K; ++q) p[q] = known ? base_letter(v >> (2 * (K - 1 - q))) : (uint8_t)'N';
-        p += K;
-    }
-}
-
 // The ids of tile t this thread holds (TPT consecutive positions; ids
 // outside the rows read as PAD, which decodes to nothing). Every load is
 // unconditional, so a thread's loads go out together: a tile inside the rows
 // reads its TPT ids as 16-byte vectors, other tiles read clamped positions
 // and select.
-template <int KIND>
 __device__ __forceinline__ int64_t load_tile_ids(const DecodeArgs &a, int64_t t, int64_t first, int64_t last,
                                                  int32_t (&idv)[TPT]) {
     const int64_t p0 = t * TT + (int64_t)threadIdx.x * TPT;
@@ -184,11 +141,11 @@ __device__ __forceinline__ int64_t load_tile_ids(const DecodeArgs &a, int64_t t,
     }
     int32_t mine = 0;  // a thread's 16 tokens of at most 2^20 bases each: 32 bits
 #pragma unroll
-    for (int j = 0; j < TPT; ++j) mine += width_of<KIND>(a, idv[j]);
+    for (int j = 0; j < TPT; ++j) mine += width_of(a, idv[j]);
     return mine;
 }
 
-// 1. The row pass: the first row of every tile, the offsets check, and the
+// BPE 1. The row pass: the first row of every tile, the offsets check, and the
 // tile status words cleared for the write pass. Row i is the first row at or
 // after position t * TT exactly for the tiles t with
 // floor(off[i-1] / TT) < t <= floor(off[i] / TT) (row n stands for the end:
@@ -202,8 +159,8 @@ __global__ __launch_bounds__(NT) void k_decode_rows(DecodeArgs a) {
         const int64_t cur = (i == a.n) ? -1 : a.offs[i];
         if (i < a.n && (cur < 0 || (i + 1 <= a.n && a.offs[i + 1] < cur) || a.offs[i + 1] > a.n_ids))
             err |= DNATOK_DERR_OFFSETS;
-        int64_t lo = (i == 0) ? 0 : (prev < 0 ? 0 : prev / a.tt + 1);
-        int64_t hi = (i == a.n) ? a.ntiles : (cur < 0 ? -1 : cur / a.tt);
+        int64_t lo = (i == 0) ? 0 : (prev < 0 ? 0 : prev / TT + 1);
+        int64_t hi = (i == a.n) ? a.ntiles : (cur < 0 ? -1 : cur / TT);
         if (hi > a.ntiles) hi = a.ntiles;
         for (int64_t t = lo; t <= hi; ++t) a.first_row[t] = i;
     }
@@ -221,31 +178,28 @@ __device__ __forceinline__ void store_stage(const DecodeArgs &a, const uint8_t *
     const int64_t room = a.cap - base;
     const int64_t lim = room <= 0 ? 0 : (room < agg ? room : agg);
     if (lim < agg) err |= DNATOK_DERR_CAPACITY;
-    const int64_t ph = (int64_t)((reinterpret_cast<uintptr_t>(a.out) + (uintptr_t)base) & 15);
+    const int32_t ph = (int32_t)((reinterpret_cast<uintptr_t>(a.out) + (uintptr_t)base) & 15);
     uint8_t *ob = a.out + base - ph;
     const uint32_t *s32 = reinterpret_cast<const uint32_t *>(s_out);
-    const int64_t nu = lim > 0 ? (ph + lim + 15) / 16 : 0;
-    for (int64_t u = tid; u < nu; u += NT) {
-        const int64_t lo = 16 * u - ph, hi = lo + 16;  // the unit's stage bytes
-        if (lo >= 0 && hi <= lim) {
+    const int32_t bytes = (int32_t)lim, nu = lim > 0 ? (ph + bytes + 15) / 16 : 0;  // lim < 2^16
+    for (int32_t u = tid; u < nu; u += NT) {
+        const int32_t lo = 16 * u - ph, hi = lo + 16;  // the unit's stage bytes
+        if (lo >= 0 && hi <= bytes) {
             const uint32_t w0 = (uint32_t)lo >> 2, r = (uint32_t)lo & 3;
             uint32_t w[5];
 #pragma unroll
             for (int q = 0; q < 5; ++q) w[q] = s32[w0 + q];
-            uint4 o;
-            o.x = __builtin_amdgcn_alignbyte(w[1], w[0], r);
-            o.y = __builtin_amdgcn_alignbyte(w[2], w[1], r);
-            o.z = __builtin_amdgcn_alignbyte(w[3], w[2], r);
-            o.w = __builtin_amdgcn_alignbyte(w[4], w[3], r);
-            *reinterpret_cast<uint4 *>(ob + 16 * u) = o;
+            u32x4 o;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) o[q] = __builtin_amdgcn_alignbyte(w[q + 1], w[q], r);
+            __builtin_nontemporal_store(o, reinterpret_cast<u32x4 *>(ob + 16 * u));
         } else {
-            for (int64_t b = (lo > 0 ? lo : 0); b < hi && b < lim; ++b) ob[ph + b] = s_out[b];
+            for (int32_t b = (lo > 0 ? lo : 0); b < hi && b < bytes; ++b) ob[ph + b] = s_out[b];
         }
     }
 }
 
-// 2. One workgroup per tile (tile = workgroup index): the tile's ids are
-// read once; their byte total is published for later tiles before the
+// BPE 2. One workgroup per tile: the tile's ids are read once; their byte total is published for later tiles before the
 // look-back, which wave 0 runs while the other waves stage the tile's bytes
 // in LDS. Once the output position is known, the block writes the output's
 // 16-byte units (each read from the stage realigned to the output's phase;
@@ -253,7 +207,6 @@ __device__ __forceinline__ void store_stage(const DecodeArgs &a, const uint8_t *
 // the flag); a tile whose output exceeds the stage writes its tokens
 // directly. Rows starting in the tile get their output offsets; the last
 // tile writes the total.
-template <int KIND>
 __global__ __launch_bounds__(NT) void k_decode_write(DecodeArgs a) {
     extern __shared__ __align__(16) uint8_t s_out[];
     __shared__ int64_t s_tpre[NT + 1];  // in-tile bytes before each thread's first position (and the total)
@@ -271,7 +224,7 @@ __global__ __launch_bounds__(NT) void k_decode_write(DecodeArgs a) {
     const int64_t first = (a.n > 0) ? a.offs[0] : 0;
     const int64_t last = (a.n > 0) ? a.offs[a.n] : 0;
     int32_t idv[TPT];
-    const int64_t mine = load_tile_ids<KIND>(a, t, first, last, idv);
+    const int64_t mine = load_tile_ids(a, t, first, last, idv);
     int64_t agg;
     const int64_t pre = dev::block_excl_scan<NT>(mine, s_tmp, &agg);
     if (tid < dev::kWave) {
@@ -295,24 +248,10 @@ __global__ __launch_bounds__(NT) void k_decode_write(DecodeArgs a) {
     if (staged) {
         // in-tile positions fit 32 bits (the stage is at most 32 KiB)
         uint32_t pos = (uint32_t)pre;
-        if (KIND == DNATOK_KMER && a.k <= 8) {
-            uint8_t *p = s_out + pos;
-            switch (a.k) {
-            case 1: stage_kmers<1>(a, idv, p); break;
-            case 2: stage_kmers<2>(a, idv, p); break;
-            case 3: stage_kmers<3>(a, idv, p); break;
-            case 4: stage_kmers<4>(a, idv, p); break;
-            case 5: stage_kmers<5>(a, idv, p); break;
-            case 6: stage_kmers<6>(a, idv, p); break;
-            case 7: stage_kmers<7>(a, idv, p); break;
-            default: stage_kmers<8>(a, idv, p); break;
-            }
-        } else {
 #pragma unroll
-            for (int j = 0; j < TPT; ++j) {
-                stage_token<KIND>(a, idv[j], s_out + pos);
-                pos += (uint32_t)width_of<KIND>(a, idv[j]);
-            }
+        for (int j = 0; j < TPT; ++j) {
+            stage_token(a, idv[j], s_out + pos);
+            pos += (uint32_t)width_of(a, idv[j]);
         }
     }
     __syncthreads();
@@ -330,8 +269,8 @@ __global__ __launch_bounds__(NT) void k_decode_write(DecodeArgs a) {
             const int64_t q = p0 + j;
             const bool live = q >= first && q < last && q < a.n_ids;
             const int32_t id = live ? a.ids[q] : DNATOK_ID_PAD;
-            write_token<KIND>(a, id, pos, err);
-            pos += width_of<KIND>(a, id);
+            write_token(a, id, pos, err);
+            pos += width_of(a, id);
         }
     }
     // rows starting in the tile: the bytes before their first position are
@@ -344,7 +283,7 @@ __global__ __launch_bounds__(NT) void k_decode_write(DecodeArgs a) {
         int64_t sum = s_tpre[th];
         for (int64_t q = P0 + (int64_t)th * TPT; q < P0 + rel; ++q) {
             const bool live = q >= first && q < last && q < a.n_ids;
-            sum += width_of<KIND>(a, live ? a.ids[q] : DNATOK_ID_PAD);
+            sum += width_of(a, live ? a.ids[q] : DNATOK_ID_PAD);
         }
         a.out_offs[i] = base + sum;
     }
@@ -353,123 +292,340 @@ __global__ __launch_bounds__(NT) void k_decode_write(DecodeArgs a) {
 }
 
 
-// 2'. The same for single-nucleotide and k-mer vocabularies up to 8 bases
-// (every token K bytes or none, a tile's output always staged), with the
-// ids strided: thread i holds the tile's ids i, i + NT, ..., so a wave's
-// lanes hold 64 consecutive ids. Loads coalesce per instruction, and a
-// staged byte store's lanes land on consecutive dwords; with each thread
-// holding 16 consecutive ids, one store's lanes were 96 bytes apart, on a
-// few LDS banks, and the staging ran bank-conflict bound beside the
-// look-back. Positions: a wave's ballot of the non-silent ids of slice j
-// gives each lane its count below it; one scan over the 64 (slice, wave)
-// counts in id order gives the rest. The ballots also give the row starts.
-template <int KIND, int K, int TPS>
-__global__ __launch_bounds__(NT) void k_decode_strided(DecodeArgs a) {
+// State of k_decode_fixed's scan over tiles: per tile its output bytes, per
+// group of 64 tiles and per super of 64 groups their sum, each word complete
+// when bit 63 is set. The last tile of a group adds its group up as soon as
+// the group's tiles have published, so a group hangs on no look-back, and the
+// position of any tile is the sum of the supers, groups and tiles before it
+// within its own super and group: two or three loads of one wave, whereas in
+// a chain of inclusive prefixes a position takes a round trip per 64 tiles
+// (2,000 resident tiles: 8 to 10 us). Words are stored, never added to:
+// 4,096 atomic adds on counters in a few lines took 200 us.
+// The words are held twice. A launch works on the half that head[0] names
+// and clears what the launch before it (head[1 + half]: its tiles) left in
+// the other; its last tile, which has seen every tile publish and so every
+// tile's read of head[0], then changes the half.
+struct ScanState {
+    uint64_t *head;  // half, tiles left in half 0, in half 1
+    uint64_t *half[2];
+    int64_t tiles, groups;  // capacity: tile words, then group words, then super words
+};
+constexpr int64_t kHeadWords = 16;
+inline int64_t scan_groups(int64_t tiles) { return (tiles + 63) / 64; }
+inline int64_t half_words(int64_t tiles) { return tiles + scan_groups(tiles) + scan_groups(scan_groups(tiles)); }
+inline int64_t scan_words(int64_t tiles) { return kHeadWords + 2 * half_words(tiles); }
+inline ScanState scan_state(uint64_t *w, int64_t tiles) {
+    return ScanState{w, {w + kHeadWords, w + kHeadWords + half_words(tiles)}, tiles, scan_groups(tiles)};
+}
+constexpr uint64_t kComplete = 1ull << 63;
+
+// Sum of the complete words p[i] for i in [lo, hi), waited for by one wave.
+// A word that stays incomplete for kLookbackMaxPolls polls raises
+// DNATOK_DERR_INTERNAL and counts what it has: every launch drains.
+__device__ __forceinline__ int64_t sum_complete(const uint64_t *p, int64_t lo, int64_t hi, uint32_t *hdr) {
+    const int lane = threadIdx.x & (dev::kWave - 1);
+    int64_t sum = 0;
+    for (int64_t j = lo; j < hi; j += dev::kWave) {
+        const bool live = j + lane < hi;
+        uint64_t w = live ? dev::ld_relaxed(p + j + lane) : kComplete;
+        uint32_t polls = 0;
+        while (__ballot(!(w & kComplete))) {
+            if (++polls >= dev::kLookbackMaxPolls) {
+                if (lane == 0) dev::raise_error(hdr, DNATOK_DERR_INTERNAL);
+                break;
+            }
+            __builtin_amdgcn_s_sleep(4);
+            if (!(w & kComplete)) w = dev::ld_relaxed(p + j + lane);
+        }
+        sum += live ? (int64_t)(w & (kComplete - 1)) : 0;
+    }
+    return dev::wave_sum(sum);
+}
+
+// Row r's offsets, checked: a tile looks at kCheckRows rows (whatever their
+// place), further workgroups at kCheckBlock of those left.
+constexpr int kCheckRows = dev::kWave, kCheckBlock = 8 * NT;
+__device__ __forceinline__ uint32_t check_rows(const DecodeArgs &a, int64_t r) {
+    if (r >= a.n) return 0;
+    const int64_t o0 = a.offs[r], o1 = a.offs[r + 1];
+    return o0 < 0 || o1 < o0 || o1 > a.n_ids ? DNATOK_DERR_OFFSETS : 0;
+}
+
+// The K letters of known k-mer code v, first letter in the low byte of w[0];
+// bytes past the K-th are zero. known false: K letters N.
+template <int K>
+__device__ __forceinline__ void letters(uint32_t v, bool known, uint32_t (&w)[(K + 3) / 4]) {
+#pragma unroll
+    for (int i = 0; i < (K + 3) / 4; ++i) {
+        constexpr int kLast = K % 4 ? K % 4 : 4;
+        const int have = i == (K + 3) / 4 - 1 ? kLast : 4, at = 2 * (K - 4 * i - 4);  // digits below the word's
+        uint32_t f = (at >= 0 ? v >> (at > 0 ? at : 0) : v << (at < 0 ? -at : 0)) & 0xFFu;
+        f = (f | (f << 12)) & 0x000F000Fu;
+        f = (f | (f << 6)) & 0x03030303u;  // digit j in byte j
+        const uint32_t x = __builtin_bswap32(__builtin_amdgcn_perm(0u, 0x54474341u, f));
+        const uint32_t mask = have == 4 ? 0xFFFFFFFFu : (1u << (8 * have)) - 1u;
+        w[i] = (known ? x : 0x4E4E4E4Eu) & mask;
+    }
+}
+
+// Single-nucleotide and k-mer ids. A wave takes U slices of 256 consecutive
+// ids, four per lane. A slice without a silent id (PAD, CLS, SEP, MASK) is
+// 256 K contiguous bytes, K dwords per lane at constant shifts; the others
+// place each id by the ballots of the non-silent ones below it. The kernel is
+// bound by the VALU beside its traffic (an instruction per id takes 0.85 us
+// for 33.6M ids): four ids in a vector, their letters from byte permutes,
+// 5 instructions per single-nucleotide id instead of the 35 that one id per
+// lane and load took. 4,096 rows of 8,192 bases: single-nucleotide ids 65 ->
+// 42 us (168 MB), 6-mers 25 -> 18 us (56 MB), in one launch instead of two.
+template <int K, int U>
+__global__ __launch_bounds__(NT) void k_decode_fixed(DecodeArgs a, ScanState st) {
     constexpr int NW = NT / dev::kWave;
-    constexpr int TPT = TPS, TT = NT * TPS;  // this kernel's ids per thread and per tile
-    constexpr int NS = TPT * NW;             // (slice, wave) entries, a multiple of the wave
+    constexpr int WT = 256 * U, FT = NW * WT;  // ids of a wave, of the tile
+    constexpr int NWORD = (K + 3) / 4;
     extern __shared__ __align__(16) uint8_t s_out[];
-    __shared__ uint32_t s_cnt[NS + 1];  // per (slice, wave): non-silent ids, then ids before; [NS]: total
-    __shared__ uint64_t s_msk[NS];      // per (slice, wave): which lanes hold a non-silent id
-    __shared__ int64_t s_ia, s_ib, s_base;
-    const int tid = threadIdx.x, lane = tid & (dev::kWave - 1), w = tid / dev::kWave;
+    __shared__ uint32_t s_wave[NW];        // non-silent ids of a wave
+    __shared__ uint32_t s_pre[NW * U];     // non-silent ids of the wave before a slice
+    __shared__ uint64_t s_silent[NW * U][4];
+    __shared__ int64_t s_po[dev::kWave];   // offsets of the rows from s_g0 on
+    __shared__ int64_t s_ia, s_g0, s_base;
+    const int tid = threadIdx.x, lane = tid & (dev::kWave - 1);
+    const int w = __builtin_amdgcn_readfirstlane(tid / dev::kWave);
     const int64_t t = blockIdx.x;
-    const int64_t P0 = t * TT;
-    if (tid == 0) {
-        int64_t ia = a.first_row[t];
-        int64_t ib = (t == a.ntiles - 1) ? a.n : a.first_row[t + 1];
-        // rows starting in the tile (clamped: bad offsets raise the flag in the row pass)
-        ia = ia < 0 ? 0 : (ia > a.n ? a.n : ia);
-        ib = ib < ia ? ia : (ib > a.n ? a.n : ib);
-        s_ia = ia;
-        s_ib = ib;
+    const int64_t P0 = t * FT;
+    const int64_t n = a.n;
+    uint32_t err = 0;
+    if (t >= a.ntiles) {  // rows that no tile checks
+        for (int64_t r = a.ntiles * kCheckRows + (t - a.ntiles) * kCheckBlock + tid; r < a.ntiles * kCheckRows + (t - a.ntiles + 1) * kCheckBlock; r += NT)
+            err |= check_rows(a, r);
+        if (err) dev::raise_error(a.err_hdr, err);
+        return;
     }
-    const int64_t first = (a.n > 0) ? a.offs[0] : 0;
-    const int64_t last = (a.n > 0) ? a.offs[a.n] : 0;
-    // ids outside the rows read as PAD (no output); loads are unconditional
-    // (clamped) so they go out together
-    int32_t idv[TPT];
+
+    ids4 id[U];
+    const int64_t p0 = P0 + w * WT + 4 * lane;
+    if (P0 + FT <= a.n_ids) {
 #pragma unroll
-    for (int j = 0; j < TPT; ++j) {
-        const int64_t p = P0 + (int64_t)j * NT + tid;
-        const bool live = p >= first && p < last && p < a.n_ids;
-        const int32_t v = a.n_ids > 0 ? a.ids[live ? p : 0] : 0;
-        idv[j] = live ? v : DNATOK_ID_PAD;
+        for (int s = 0; s < U; ++s) id[s] = __builtin_nontemporal_load(reinterpret_cast<const ids4 *>(a.ids + p0 + 256 * s));
+    } else {
+#pragma unroll
+        for (int s = 0; s < U; ++s)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const int64_t p = p0 + 256 * s + q;
+                id[s][q] = p < a.n_ids ? a.ids[p] : DNATOK_ID_PAD;
+            }
     }
-    uint32_t below[TPT];  // non-silent ids of this slice and wave below this lane
+    const int64_t first = n > 0 ? a.offs[0] : 0, last = n > 0 ? a.offs[n] : 0;
+    const uint64_t half = dev::ld_relaxed(st.head) & 1u;
+    const int64_t left = (int64_t)dev::ld_relaxed(st.head + 2 - half);  // tiles left in the other half
+    uint64_t *tile_word = half ? st.half[1] : st.half[0], *other = half ? st.half[0] : st.half[1];
+    uint64_t *group_word = tile_word + st.tiles, *super_word = group_word + st.groups;
+    int64_t g0 = 0, po = 0;  // 64 rows around the one the tile would start in if rows were equally long
+    if (w == NW - 1) {
+        err |= check_rows(a, t * kCheckRows + lane);
+        g0 = (int64_t)((double)P0 * a.rows_per_id) - dev::kWave / 2;
+        if (g0 + dev::kWave > n) g0 = n - dev::kWave;
+        if (g0 < 0) g0 = 0;
+        po = a.offs[min(g0 + lane, n)];
+    }
+    if (P0 < first || P0 + FT > last) {  // ids outside the rows decode to nothing
 #pragma unroll
-    for (int j = 0; j < TPT; ++j) {
-        const uint64_t m = __ballot(!is_silent(idv[j]));
-        below[j] = __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+        for (int s = 0; s < U; ++s)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const int64_t p = p0 + 256 * s + q;
+                if (p < first || p >= last) id[s][q] = DNATOK_ID_PAD;
+            }
+    }
+    uint32_t mine = 0, pre[U];
+    bool gaps[U];
+#pragma unroll
+    for (int s = 0; s < U; ++s) {
+        const uint32_t lowest = min(min((uint32_t)id[s][0], (uint32_t)id[s][1]), min((uint32_t)id[s][2], (uint32_t)id[s][3]));
+        gaps[s] = __ballot(lowest < 5u) != 0;  // (an UNK is not silent, but rare)
+        pre[s] = mine;
+        uint64_t m[4] = {0, 0, 0, 0};
+        mine += 256;
+        if (gaps[s]) {
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                m[q] = __ballot(is_silent(id[s][q]));
+                mine -= (uint32_t)__popcll(m[q]);
+            }
+        }
         if (lane == 0) {
-            s_cnt[j * NW + w] = (uint32_t)__popcll(m);
-            s_msk[j * NW + w] = m;
+            s_pre[w * U + s] = pre[s];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) s_silent[w * U + s][q] = m[q];
         }
     }
+    if (lane == 0) s_wave[w] = mine;
     __syncthreads();
-    if (tid < dev::kWave) {  // ids before each (slice, wave), in id order; a lane takes NS / 64 in a row
-        constexpr int PER = NS / dev::kWave;
-        uint32_t v[PER], sum = 0;
+    uint32_t before = 0, total = 0;  // of the waves before this one, of the tile
 #pragma unroll
-        for (int q = 0; q < PER; ++q) {
-            v[q] = s_cnt[tid * PER + q];
-            sum += v[q];
-        }
-        const uint32_t inc = dev::wave_incl_sum_u32(sum);
-        uint32_t run = inc - sum;
-#pragma unroll
-        for (int q = 0; q < PER; ++q) {
-            s_cnt[tid * PER + q] = run;
-            run += v[q];
-        }
-        if (tid == dev::kWave - 1) s_cnt[NS] = inc;
+    for (int i = 0; i < NW; ++i) {
+        before += i < w ? s_wave[i] : 0;
+        total += s_wave[i];
     }
-    __syncthreads();
-    const int64_t agg = (int64_t)K * s_cnt[NS];
-    if (tid < dev::kWave) {
-        if (tid == 0) dev::publish_aggregate(a.status, t, agg);
-        const int64_t excl = dev::wave_lookback(a.status, t, agg, a.err_hdr);
-        if (tid == 0) s_base = excl;
+    const int64_t agg = (int64_t)K * total, g = t / 64, sp = g / 64;
+    if (w == 0 && lane == 0) dev::st_relaxed(tile_word + t, kComplete | (uint64_t)agg);
+    for (int64_t i = t * NT + tid; i < left; i += a.ntiles * NT) {
+        dev::st_relaxed(other + i, 0);
+        if (i % 64 == 0) dev::st_relaxed(other + st.tiles + i / 64, 0);
+        if (i % 4096 == 0) dev::st_relaxed(other + st.tiles + st.groups + i / 4096, 0);
     }
-    // the bytes go to LDS while wave 0 still waits on the look-back
+    if (w == NW - 1) {  // the first row that starts in the tile
+        auto pred = [&](int64_t r) { return a.offs[r] >= P0; };
+        const uint64_t hit = __ballot(g0 + lane < n ? po >= P0 : true);
+        int64_t ia;
+        if ((hit & 1ull) && g0 > 0) ia = dev::wave_lower_bound(0, g0, pred);
+        else if (hit == 0) ia = dev::wave_lower_bound(g0 + dev::kWave, n, pred);
+        else ia = g0 + __builtin_ctzll(hit);
+        s_po[lane] = po;
+        if (lane == 0) {
+            s_ia = min(ia, n);
+            s_g0 = g0;
+        }
+    }
+    // the bytes to LDS
 #pragma unroll
-    for (int j = 0; j < TPT; ++j) {
-        const int32_t id = idv[j];
-        if (is_silent(id)) continue;
-        uint8_t *p = s_out + (uint32_t)K * (s_cnt[j * NW + w] + below[j]);
-        if (KIND == DNATOK_SINGLE) {
-            p[0] = single_letter(id);
+    for (int s = 0; s < U; ++s) {
+        uint8_t *p = s_out + (uint32_t)K * (before + pre[s]);
+        if (!gaps[s]) {
+            uint32_t out[K];
+            if constexpr (K == 1) {
+                uint32_t sel = 0;
+#pragma unroll
+                for (int q = 0; q < 4; ++q) sel |= min((uint32_t)id[s][q] - 5u, 4u) << (8 * q);
+                out[0] = __builtin_amdgcn_perm(0x4E4E4E4Eu, 0x54474341u, sel);
+            } else {
+#pragma unroll
+                for (int i = 0; i < K; ++i) out[i] = 0;
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    uint32_t x[NWORD];
+                    const uint32_t v = (uint32_t)id[s][q] - 5u;
+                    letters<K>(v, v < a.codes, x);
+#pragma unroll
+                    for (int i = 0; i < NWORD; ++i) {
+                        const int at = q * K + 4 * i, sh = 8 * (at % 4);
+                        const int bytes = i == NWORD - 1 ? K - 4 * i : 4;
+                        out[at / 4] |= x[i] << sh;
+                        if (sh / 8 + bytes > 4) out[at / 4 + 1] |= x[i] >> (32 - sh);
+                    }
+                }
+            }
+            __builtin_memcpy(p + 4 * K * lane, out, 4 * K);
         } else {
-            const bool known = id >= 5 && id < a.vocab;
-            const uint32_t v = (uint32_t)(id - 5);
+            uint32_t below = 0;
 #pragma unroll
-            for (int q = 0; q < K; ++q) p[q] = known ? base_letter(v >> (2 * (K - 1 - q))) : (uint8_t)'N';
+            for (int q = 0; q < 4; ++q) {
+                const uint64_t m = ~s_silent[w * U + s][q];
+                below += __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+            }
+            p += (uint32_t)K * below;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                if (is_silent(id[s][q])) continue;
+                uint32_t x[NWORD];
+                const uint32_t v = (uint32_t)id[s][q] - 5u;
+                letters<K>(v, v < a.codes, x);
+                __builtin_memcpy(p, x, K);
+                p += K;
+            }
         }
+    }
+    if (w == 0) {
+        // nearest first: the older words are then there already
+        int64_t sum = sum_complete(tile_word, g * 64, t, a.err_hdr);
+        if (t % 64 == 63 && lane == 0) dev::st_relaxed(group_word + g, kComplete | (uint64_t)(sum + agg));
+        const int64_t in_super = sum_complete(group_word, sp * 64, g, a.err_hdr);
+        sum += in_super;
+        if (t % 4096 == 4095 && lane == 0) dev::st_relaxed(super_word + sp, kComplete | (uint64_t)(sum + agg));
+        sum += sum_complete(super_word, 0, sp, a.err_hdr);
+        if (lane == 0) s_base = sum;
     }
     __syncthreads();
     const int64_t base = s_base;
-    uint32_t err = 0;
     store_stage(a, s_out, base, agg, err);
     // rows starting in the tile: K bytes per non-silent id before their first position
-    for (int64_t i = s_ia + tid; i < s_ib; i += NT) {
-        int64_t rel = a.offs[i] - P0;
-        rel = rel < 0 ? 0 : (rel > TT ? TT : rel);
-        uint32_t c = s_cnt[NS];
-        if (rel < TT) {
-            const int js = (int)(rel / NT), ws = (int)((rel % NT) / dev::kWave), l = (int)(rel % dev::kWave);
-            c = s_cnt[js * NW + ws] + (uint32_t)__popcll(s_msk[js * NW + ws] & ((1ull << l) - 1ull));
+    const int64_t w0 = s_g0;
+    for (int64_t i = s_ia + tid; i < n; i += NT) {
+        const int64_t o = i >= w0 && i - w0 < dev::kWave ? s_po[i - w0] : a.offs[i];
+        if (o >= P0 + FT && t < a.ntiles - 1) break;
+        const int32_t rel = (int32_t)min(max(o - P0, (int64_t)0), (int64_t)FT);
+        uint32_t c = total;
+        if (rel < FT) {
+            const int sl = rel / 256, l = (rel % 256) / 4, q0 = rel % 4;
+            c = s_pre[sl] + (uint32_t)(rel % 256);
+            for (int i2 = 0; i2 < sl / U; ++i2) c += s_wave[i2];
+            for (int q = 0; q < 4; ++q) {
+                const uint64_t m = s_silent[sl][q];
+                c -= (uint32_t)__popcll(m & ((1ull << l) - 1ull));
+                if (q < q0) c -= (uint32_t)(m >> l) & 1u;
+            }
         }
         a.out_offs[i] = base + (int64_t)K * c;
     }
-    if (t == a.ntiles - 1 && tid == 0) a.out_offs[a.n] = base + agg;
     if (err) dev::raise_error(a.err_hdr, err);
+    if (t == a.ntiles - 1 && tid == 0) {
+        a.out_offs[n] = base + agg;
+        dev::st_relaxed(st.head + 1 + half, (uint64_t)a.ntiles);
+        dev::st_relaxed(st.head, half ^ 1u);
+    }
+}
+
+static_assert(kDecodeWords == kHeadWords + 2 * (kDecodeTiles + kDecodeTiles / 64 + kDecodeTiles / 4096), "the workspace's words");
+
+__global__ void k_clear_words(uint64_t *p, int64_t n) {
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
+        p[i] = 0;
+}
+
+template <int K>
+int launch_fixed(DecodeArgs a, Workspace *ws, hipStream_t stream) {
+    // Ids per tile: 1,024 times U. Tiles that do not all fit the card at once
+    // wait for a second set of prefixes, 6 us; large tiles leave fewer waves.
+    // So the smallest U with at most 7 tiles per CU (single letters 5), up to
+    // what a stage of 48 KiB holds. Measured, in us at U = 2 / 4 / 8 / 16:
+    // 6.7M 5-mers 24.7 / 18.2 / 23.9 / -, 10M single letters - / 21.9 / 17.4 /
+    // 20.4, 3M 11.1 / 10.1 / 10.0 / -, 33.6M 61 / 56 / 43.1 / 40.5.
+    constexpr int UMAX = K == 1 ? 16 : K <= 6 ? 8 : K <= 12 ? 4 : 2;
+    static_assert(1024 * UMAX * K <= 49152, "three tiles' stages fit a CU");
+    int U = 1;
+    while (U < UMAX && a.n_ids > 1024 * (int64_t)U * (K == 1 ? 5 : 7) * device_cu_count()) U <<= 1;
+    a.ntiles = a.n_ids / (1024 * U) + 1;
+    if (a.ntiles >= (1ll << 31)) return set_error(DNATOK_EINVAL, "too many ids for one decode");
+    a.rows_per_id = a.n_ids > 0 ? (double)a.n / (double)a.n_ids : 0.0;
+    a.codes = 1u << (2 * K);
+    ScanState st = scan_state(ws->d_decode, kDecodeTiles);
+    if (!ws->d_decode || a.ntiles > kDecodeTiles) {
+        const int64_t nw = scan_words(a.ntiles);
+        int rc = ensure_scratch(ws, 8 * nw);
+        if (rc) return rc;
+        st = scan_state(reinterpret_cast<uint64_t *>(ws->d_scratch), a.ntiles);
+        hipLaunchKernelGGL(k_clear_words, dim3((unsigned)std::min<int64_t>((nw + 255) / 256, 1024)), dim3(256), 0, stream, st.head, nw);
+        DNATOK_HIP(hipGetLastError());
+    }
+    const int64_t unchecked = std::max<int64_t>(0, a.n - a.ntiles * kCheckRows);
+    const dim3 grid((unsigned)(a.ntiles + (unchecked + kCheckBlock - 1) / kCheckBlock)), block(NT);
+    const size_t dyn = (size_t)1024 * U * K + 16;  // a unit's realigning reads go up to 3 bytes past the data
+    switch (U) {
+    case 1: hipLaunchKernelGGL((k_decode_fixed<K, 1>), grid, block, dyn, stream, a, st); break;
+    case 2: hipLaunchKernelGGL((k_decode_fixed<K, 2>), grid, block, dyn, stream, a, st); break;
+    case 4: if constexpr (UMAX >= 4) hipLaunchKernelGGL((k_decode_fixed<K, 4>), grid, block, dyn, stream, a, st); break;
+    case 8: if constexpr (UMAX >= 8) hipLaunchKernelGGL((k_decode_fixed<K, 8>), grid, block, dyn, stream, a, st); break;
+    default: if constexpr (UMAX >= 16) hipLaunchKernelGGL((k_decode_fixed<K, 16>), grid, block, dyn, stream, a, st); break;
+    }
+    DNATOK_HIP(hipGetLastError());
+    return DNATOK_OK;
 }
 
 }  // namespace
 
 int launch_decode(const dnatok_vocab *v, const int32_t *d_ids, int64_t n_ids, const int64_t *d_offsets, int32_t n,
                   uint8_t *d_out, int64_t out_capacity, int64_t *d_out_offsets, hipStream_t stream) {
-    DecodeArgs a;
+    DecodeArgs a = {};
     a.ids = d_ids;
     a.n_ids = n_ids;
     a.offs = d_offsets;
@@ -483,44 +639,43 @@ int launch_decode(const dnatok_vocab *v, const int32_t *d_ids, int64_t n_ids, co
     a.tok_len = v->bpe.d_tok_len;
     a.tok_off = v->bpe.d_tok_off;
     a.tok_chars = v->bpe.d_tok_chars;
-    // single-nucleotide ids go 32 per thread (8,192 per tile): half the tiles'
-    // fixed latency for a stage of 8 KiB (73 -> 58 us for 33.6M ids)
-    a.tt = v->kind == DNATOK_SINGLE ? (int64_t)TT_SINGLE : (int64_t)TT;
-    a.ntiles = n_ids / a.tt + 1;
-    if (a.ntiles >= (1ll << 31)) return set_error(DNATOK_EINVAL, "too many ids for one decode");
-    // the stage holds a tile's output at the vocabulary's widest token
-    const int64_t wmax = v->kind == DNATOK_KMER ? v->k : (v->kind == DNATOK_BPE ? v->max_token_bytes : 1);
-    a.stage = (int32_t)std::min<int64_t>(a.tt * std::max<int64_t>(wmax, 1), kMaxStage);
     Workspace *ws = nullptr;
     int rc = get_workspace(stream, 1, &ws);
     if (rc) return rc;
+    a.err_hdr = ws->d_hdr;
+    if (v->kind != DNATOK_BPE) {
+        switch (v->kind == DNATOK_KMER ? v->k : 1) {
+        case 1: return launch_fixed<1>(a, ws, stream);
+        case 2: return launch_fixed<2>(a, ws, stream);
+        case 3: return launch_fixed<3>(a, ws, stream);
+        case 4: return launch_fixed<4>(a, ws, stream);
+        case 5: return launch_fixed<5>(a, ws, stream);
+        case 6: return launch_fixed<6>(a, ws, stream);
+        case 7: return launch_fixed<7>(a, ws, stream);
+        case 8: return launch_fixed<8>(a, ws, stream);
+        case 9: return launch_fixed<9>(a, ws, stream);
+        case 10: return launch_fixed<10>(a, ws, stream);
+        case 11: return launch_fixed<11>(a, ws, stream);
+        case 12: return launch_fixed<12>(a, ws, stream);
+        case 13: return launch_fixed<13>(a, ws, stream);
+        case 14: return launch_fixed<14>(a, ws, stream);
+        default: return launch_fixed<15>(a, ws, stream);
+        }
+    }
+    a.ntiles = n_ids / TT + 1;
+    if (a.ntiles >= (1ll << 31)) return set_error(DNATOK_EINVAL, "too many ids for one decode");
+    // the stage holds a tile's output at the vocabulary's widest token
+    a.stage = (int32_t)std::min<int64_t>((int64_t)TT * std::max<int64_t>(v->max_token_bytes, 1), kMaxStage);
     rc = ensure_scratch(ws, 16 * (a.ntiles + 1));
     if (rc) return rc;
     a.status = reinterpret_cast<uint64_t *>(ws->d_scratch);
     a.first_row = reinterpret_cast<int64_t *>(a.status + (a.ntiles + 1));
-    a.err_hdr = ws->d_hdr;
     const int64_t rows_grid = std::min<int64_t>(((int64_t)n + 1 + NT - 1) / NT + 1, 4ll * device_cu_count());
     hipLaunchKernelGGL(k_decode_rows, dim3((unsigned)std::max<int64_t>(rows_grid, 1)), dim3(NT), 0, stream, a);
     DNATOK_HIP(hipGetLastError());
     const dim3 grid((unsigned)a.ntiles), block(NT);
     const size_t dyn = (size_t)a.stage + 16;  // a unit's realigning reads go up to 3 bytes past the data
-    if (v->kind == DNATOK_SINGLE) {  // its stage (a.tt bytes) always holds the tile
-        hipLaunchKernelGGL((k_decode_strided<DNATOK_SINGLE, 1, TPT_SINGLE>), grid, block, dyn, stream, a);
-    } else if (v->kind == DNATOK_KMER && v->k <= 8 && a.stage >= TT * v->k) {
-        switch (v->k) {
-        case 1: hipLaunchKernelGGL((k_decode_strided<DNATOK_KMER, 1, TPT>), grid, block, dyn, stream, a); break;
-        case 2: hipLaunchKernelGGL((k_decode_strided<DNATOK_KMER, 2, TPT>), grid, block, dyn, stream, a); break;
-        case 3: hipLaunchKernelGGL((k_decode_strided<DNATOK_KMER, 3, TPT>), grid, block, dyn, stream, a); break;
-        case 4: hipLaunchKernelGGL((k_decode_strided<DNATOK_KMER, 4, TPT>), grid, block, dyn, stream, a); break;
-        case 5: hipLaunchKernelGGL((k_decode_strided<DNATOK_KMER, 5, TPT>), grid, block, dyn, stream, a); break;
-        case 6: hipLaunchKernelGGL((k_decode_strided<DNATOK_KMER, 6, TPT>), grid, block, dyn, stream, a); break;
-        case 7: hipLaunchKernelGGL((k_decode_strided<DNATOK_KMER, 7, TPT>), grid, block, dyn, stream, a); break;
-        default: hipLaunchKernelGGL((k_decode_strided<DNATOK_KMER, 8, TPT>), grid, block, dyn, stream, a); break;
-        }
-    } else if (v->kind == DNATOK_KMER)
-        hipLaunchKernelGGL(k_decode_write<DNATOK_KMER>, grid, block, dyn, stream, a);
-    else
-        hipLaunchKernelGGL(k_decode_write<DNATOK_BPE>, grid, block, dyn, stream, a);
+    hipLaunchKernelGGL(k_decode_write, grid, block, dyn, stream, a);
     DNATOK_HIP(hipGetLastError());
     return DNATOK_OK;
 }
