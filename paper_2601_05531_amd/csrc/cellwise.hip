@@ -11,13 +11,14 @@
 // MI355X-first decomposition. The output dominates the traffic: an embedding
 // row of D values per token (256 bytes for D = 128 in bf16, against about one
 // input byte). Work is therefore cut by output cells rather than input tiles:
-//  * A block takes chunks of NT * CPT consecutive cells (cells = tokens plus
-//    pads); each thread takes CPT consecutive cells of the chunk, so its ids
-//    go out as one 16-byte store and its mask bytes as one word. The thread
+//  * A block takes a tile of about 32 KiB of output (4 to 1,024 consecutive
+//    cells; cells = tokens plus pads), a thread CPT consecutive cells, so its
+//    ids go out as one 16-byte store and its mask bytes as one word. Every
+//    XCD takes one contiguous part of the tiles. A thread
 //    finds the row of its first cell (PADDED: cell / W with a 32-bit
-//    reciprocal; PACKED: the chunk's first and last rows by one-wave 64-way
-//    searches over the row starts the row scan wrote, then a binary search
-//    between them) and steps to the next row only at a row end. It places
+//    reciprocal; PACKED: its wave's first and last rows by 64-way searches
+//    over the row starts the row scan wrote, then a binary search between
+//    them) and steps to the next row only at a row end. It places
 //    every cell first (pad, CLS, SEP or body token, and the bytes a body
 //    token reads), then issues all of its reads at once: a k-mer reads the
 //    three (k <= 8) or five dwords that hold it and classifies them with
@@ -25,12 +26,16 @@
 //    reverses and complements the digits in registers (the bytes are never
 //    rewritten), and for table kinds it reads a table already mapped
 //    through the complement.
-//  * The chunk's ids go to LDS and the block copies
-//    the table rows out in UB-byte units (UB = 16 whenever the row size and
+//  * The tile's table rows go to LDS and the block copies
+//    them out in UB-byte units (UB = 16 whenever the row size and
 //    pointers allow): lane l of a wave moves unit l, so a wave writes 1 KiB
 //    of contiguous output per instruction. Several units are loaded before
 //    any is stored. Table rows are read through L2 (a 4101 x 256-byte table
 //    is 1 MiB, resident there); the output is the only HBM stream.
+// The store pattern bounds it: the same stores without the lookup take 101 of
+// 103 us when 256 KiB belong to a block in grid order. 4,096 rows of 512
+// bases, 256-byte table rows (541 MB): 103 -> 86 us, a fill of it 78; 300 rows
+// of 3,000 bases as 6-mers: 18.7 -> 13.9; 16 of 1,000: 15.3 -> 6.8.
 // Bounds: every output index is below the capacity the caller gave; bad
 // offsets are clamped exactly as the row scan clamps them, so cell positions
 // and the written offsets agree.
@@ -44,11 +49,11 @@ namespace {
 
 constexpr int NT = 256;
 static_assert(NT == kScanNT, "the fused row scan runs with the cell kernel's block size");
-constexpr int32_t kFuseMaxRows = 16384;      // PADDED: the first block scans the rows instead of a separate launch
-constexpr int kGridPerSlot = 4;              // blocks launched per resident block slot
-constexpr int CPT = 4;                       // cells per thread per chunk (a multiple of 4)
-constexpr int64_t kChunk = (int64_t)NT * CPT;
-constexpr int kCopyUnroll = 4;               // table units loaded before they are stored
+constexpr int64_t kMaxGrid = 1 << 20;        // workgroups of cells
+constexpr int CPT = 4;                       // cells per thread (a multiple of 4)
+constexpr int kMaxCells = NT * CPT;          // cells of a tile
+constexpr int kTileBytes = 32768;            // output of a tile, where kMaxCells allows
+constexpr int kCopyUnroll = 8;               // table units loaded before they are stored
 
 enum CwMode { CW_EMBED = 1, CW_GATHER = 2 };
 
@@ -58,6 +63,7 @@ struct CwArgs {
     const int64_t *offs;
     int32_t n;
     int32_t lut_kind;        // 1: id = lut[byte] (SINGLE, LUT256); 0: k-mer windows
+    int64_t *scan_out;       // out_offsets, written by the scanning workgroups
     const int64_t *out_offs; // PACKED row starts (offset_base included)
     int64_t base;
     int64_t ncells;          // PADDED: n * W; GATHER: n_ids; PACKED: -1 (read out_offs[n])
@@ -81,9 +87,10 @@ struct CwArgs {
     int64_t row_bytes;
     uint8_t *emb;
     uint32_t ru, ruinv;      // units per table row and floor((2^32 - 1) / ru)
+    uint32_t step_cell, step_part;  // NT units in rows and units
     uint32_t *err_hdr;
-    int32_t fused_scan;      // PADDED, few rows: block 0 writes out_offsets (the others take cells)
-    RowScanArgs scan;
+    int32_t cells;           // cells of a tile, a multiple of CPT
+    int32_t scan_units;      // PADDED, up to kIndependentMaxRows rows: the first workgroups scan the rows
 };
 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
@@ -228,13 +235,13 @@ __device__ __forceinline__ int64_t packed_row(const CwArgs &a, int64_t lo, int64
 // cells only at row ends.
 template <bool K8>
 __device__ __forceinline__ void thread_cells(const CwArgs &a, const int32_t *s_lut, int64_t cb, int64_t cend,
-                                             const int64_t *s_rows, int32_t (&id)[CPT], bool (&tok)[CPT]) {
+                                             int64_t r0, int64_t r1, int32_t (&id)[CPT], bool (&tok)[CPT]) {
     int64_t row, p;
     if (a.padded) {
         row = div_any(cb, a.W, a.winv);
         p = cb - row * a.W;
     } else {
-        row = packed_row(a, s_rows[0], s_rows[1], cb);
+        row = packed_row(a, r0, r1, cb);
         p = cb - (a.out_offs[row] - a.base);
     }
     RowFacts f = row_facts(a, row);
@@ -370,16 +377,17 @@ __device__ __forceinline__ void thread_cells(const CwArgs &a, const int32_t *s_l
 template <int MODE, int UB, bool K8>
 __global__ __launch_bounds__(NT) void k_cellwise(CwArgs a) {
     __shared__ int32_t s_lut[256];
-    __shared__ int32_t s_id[kChunk];
-    __shared__ int64_t s_rows[2];
+    __shared__ int64_t s_row[kMaxCells];  // table row of a cell, in bytes; -1: none
     const int tid = threadIdx.x;
-    if (MODE != CW_GATHER && a.fused_scan && blockIdx.x == 0) {
+    const int w = __builtin_amdgcn_readfirstlane(tid / dev::kWave);
+    if (MODE != CW_GATHER && (int)blockIdx.x < a.scan_units) {
         __shared__ int64_t s_tmp[kScanNT / dev::kWave + 1];
-        rowscan_single_block(a.scan, s_tmp, a.err_hdr);
+        rowscan_independent(RowLen{a.offs, a.nbytes, a.n, a.k, a.kinv, a.lut_kind ? 0 : 1, a.overlap, a.cls, a.W},
+                            a.scan_out, a.base, (int)blockIdx.x, s_tmp, a.err_hdr);
         return;
     }
-    const int64_t bid = (int64_t)blockIdx.x - a.fused_scan;  // cell walker index
-    const int64_t G = (int64_t)gridDim.x - a.fused_scan;     // cell walkers
+    const int64_t bid = (int64_t)blockIdx.x - a.scan_units;
+    const int64_t G = (int64_t)gridDim.x - a.scan_units;
     if (MODE != CW_GATHER) s_lut[tid] = a.lut[a.revcomp ? complement((uint32_t)tid) : (uint32_t)tid];
     int64_t total = a.ncells;
     if (total < 0) total = a.out_offs[a.n] - a.base;
@@ -388,20 +396,21 @@ __global__ __launch_bounds__(NT) void k_cellwise(CwArgs a) {
     uint32_t err = 0;
     __syncthreads();
 
-    for (int64_t c0 = bid * kChunk; c0 < limit; c0 += G * kChunk) {
-        const int64_t cend = limit - c0 < kChunk ? limit : c0 + kChunk;
-        if (MODE != CW_GATHER && !a.padded) {
-            // the chunk's first and last rows, one wave each
-            const int w = tid / dev::kWave;
-            if (w < 2) {
-                const int64_t key = w == 0 ? c0 : cend - 1;
-                const int64_t r = dev::wave_lower_bound(0, a.n, [&](int64_t q) { return a.out_offs[q + 1] - a.base > key; });
-                if ((tid & (dev::kWave - 1)) == 0) s_rows[w] = r;
-            }
-            __syncthreads();
+    // (one tile per block up to kMaxGrid blocks)
+    for (int64_t c0 = dev::xcd_tile(bid, G) * a.cells; c0 < limit; c0 += G * a.cells) {
+        const int64_t cend = limit - c0 < a.cells ? limit : c0 + a.cells;
+        int64_t r0 = 0, r1 = 0;  // PACKED: rows of the tile's first and last cell
+        const int64_t wb = c0 + w * dev::kWave * CPT;  // the wave's cells
+        if (MODE != CW_GATHER && !a.padded && wb < cend) {
+            const int64_t we = min(wb + dev::kWave * CPT, cend) - 1;
+            auto past = [&](int64_t key) {
+                return [&a, key](int64_t q) { return a.out_offs[q + 1] - a.base > key; };
+            };
+            r0 = dev::wave_lower_bound(0, a.n, past(wb));
+            r1 = past(we)(r0) ? r0 : dev::wave_lower_bound(r0, a.n, past(we));
         }
         // this thread's CPT consecutive cells
-        const int64_t cb = c0 + (int64_t)tid * CPT;
+        const int64_t cb = c0 + tid * CPT;
         int32_t id[CPT];
         bool tok[CPT];
 #pragma unroll
@@ -422,7 +431,7 @@ __global__ __launch_bounds__(NT) void k_cellwise(CwArgs a) {
                 }
             }
         } else if (cb < cend) {
-            thread_cells<K8>(a, s_lut, cb, cend, s_rows, id, tok);
+            thread_cells<K8>(a, s_lut, cb, cend, r0, r1, id, tok);
         }
         if (MODE != CW_GATHER && cb < cend) {
             const bool full = cb + CPT <= cend;
@@ -452,28 +461,30 @@ __global__ __launch_bounds__(NT) void k_cellwise(CwArgs a) {
             }
         }
 #pragma unroll
-        for (int i = 0; i < CPT; ++i) s_id[tid * CPT + i] = id[i];
+        for (int i = 0; i < CPT; ++i) s_row[tid * CPT + i] = id[i] >= 0 ? (int64_t)id[i] * a.row_bytes : -1;
         typedef typename Unit<UB>::T V;
         __syncthreads();
         const uint32_t units = (uint32_t)(cend - c0) * a.ru;
         uint8_t *ob = a.emb + c0 * a.row_bytes;
+        uint32_t cell = udiv(tid, a.ru, a.ruinv), part = tid - cell * a.ru;
         for (uint32_t u0 = tid; u0 < units; u0 += NT * kCopyUnroll) {
             V v[kCopyUnroll];
-            uint32_t cell[kCopyUnroll], part[kCopyUnroll];
 #pragma unroll
             for (int t = 0; t < kCopyUnroll; ++t) {
-                const uint32_t u = u0 + t * NT;
-                cell[t] = udiv(u, a.ru, a.ruinv);
-                part[t] = u - cell[t] * a.ru;
-                const int32_t rid = u < units ? s_id[cell[t]] : -1;
-                if (rid >= 0) v[t] = *reinterpret_cast<const V *>(a.table + (int64_t)rid * a.row_bytes + part[t] * UB);
+                const int64_t row = u0 + t * NT < units ? s_row[cell] : -1;
+                if (row >= 0) v[t] = *reinterpret_cast<const V *>(a.table + row + part * UB);
                 else v[t] = V{};
+                cell += a.step_cell;  // the unit NT further on
+                part += a.step_part;
+                if (part >= a.ru) {
+                    part -= a.ru;
+                    ++cell;
+                }
             }
 #pragma unroll
             for (int t = 0; t < kCopyUnroll; ++t) {
                 const uint32_t u = u0 + t * NT;
-                if (u < units)
-                    __builtin_nontemporal_store(v[t], reinterpret_cast<V *>(ob + (int64_t)cell[t] * a.row_bytes + part[t] * UB));
+                if (u < units) __builtin_nontemporal_store(v[t], reinterpret_cast<V *>(ob) + u);
             }
         }
         __syncthreads();
@@ -483,15 +494,7 @@ __global__ __launch_bounds__(NT) void k_cellwise(CwArgs a) {
 
 template <int MODE, int UB, bool K8>
 int launch_cw(const CwArgs &a, int64_t max_cells, hipStream_t stream) {
-    int per_cu = 0;
-    DNATOK_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_cellwise<MODE, UB, K8>, NT, 0));
-    // several blocks per resident slot: a block that ends need not wait for
-    // its stores, where a walker's next chunk would
-    int64_t g = kGridPerSlot * (int64_t)device_cu_count() * (per_cu > 0 ? per_cu : 1);
-    const int64_t chunks = (max_cells + kChunk - 1) / kChunk;
-    if (g > chunks) g = chunks;
-    if (g < 1) g = 1;
-    g += a.fused_scan;
+    const int64_t g = std::min(std::max<int64_t>(1, (max_cells + a.cells - 1) / a.cells), kMaxGrid) + a.scan_units;
     hipLaunchKernelGGL((k_cellwise<MODE, UB, K8>), dim3((unsigned)g), dim3(NT), 0, stream, a);
     DNATOK_HIP(hipGetLastError());
     return DNATOK_OK;
@@ -513,6 +516,9 @@ int launch_cw_units(CwArgs &a, int64_t max_cells, hipStream_t stream) {
     while (ub > 1 && (al & (uintptr_t)(ub - 1))) ub >>= 1;
     a.ru = (uint32_t)(a.row_bytes / ub);
     a.ruinv = 0xFFFFFFFFu / a.ru;
+    a.step_cell = NT / a.ru;
+    a.step_part = NT % a.ru;
+    a.cells = (int32_t)std::min<int64_t>(kMaxCells, std::max<int64_t>(CPT, kTileBytes / a.row_bytes / CPT * CPT));
     switch (ub) {
     case 16: return launch_cw_k<MODE, 16>(a, max_cells, stream);
     case 8: return launch_cw_k<MODE, 8>(a, max_cells, stream);
@@ -554,23 +560,9 @@ int setup_encode(CwArgs &a, const dnatok_vocab *v, const uint8_t *d_bytes, int64
     Workspace *ws = nullptr;
     int rc = get_workspace(stream, 1, &ws);
     if (rc) return rc;
-    a.fused_scan = (a.padded && n <= kFuseMaxRows) ? 1 : 0;
-    if (a.fused_scan) {
-        RowScanArgs &sc = a.scan;
-        sc = RowScanArgs{};
-        sc.offs = d_offsets;
-        sc.n = n;
-        sc.nbytes = nbytes;
-        sc.out_offs = d_out_offsets;
-        sc.k = a.k;
-        sc.kinv = a.kinv;
-        sc.kmer = kmer ? 1 : 0;
-        sc.overlap = a.overlap;
-        sc.cls = a.cls;
-        sc.padded = 1;
-        sc.W = a.W;
-        sc.base = a.base;
-    } else {
+    a.scan_units = a.padded && n <= kIndependentMaxRows ? (int32_t)rowscan_units(n) : 0;
+    a.scan_out = d_out_offsets;
+    if (!a.scan_units) {
         RowScanSpec sp;
         sp.offs = d_offsets;
         sp.n = n;

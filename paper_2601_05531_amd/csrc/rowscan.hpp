@@ -174,21 +174,6 @@ constexpr int32_t kIndependentMaxRows = 65536;
     if (err) dev::raise_error(err_hdr, err);
 }
 
-// Whole batch by one block, units in order (the fused PADDED case).
-[[maybe_unused]] __device__ void rowscan_single_block(const RowScanArgs &a, int64_t *s_tmp, uint32_t *err_hdr) {
-    uint32_t err = 0;
-    int64_t run = 0;
-    for (int64_t row0 = 0; row0 < a.n; row0 += kUnitRows) {
-        rowscan_unit(a, row0, s_tmp, err, [&](int64_t total) {
-            const int64_t b = run;
-            run += total;
-            return b;
-        });
-    }
-    if (threadIdx.x == 0) a.out_offs[a.n] = a.base + run;
-    if (err) dev::raise_error(err_hdr, err);
-}
-
 }  // namespace
 
 }  // namespace dnatok
