@@ -269,7 +269,8 @@ def dnatok_vocab_info(handle: int):
 
 def dnatok_encode_plan(handle: int, h_offsets: np.ndarray, n: int, opts: dnatok_encode_opts):
     tot, mx = ctypes.c_int64(), ctypes.c_int64()
-    h_offsets = np.ascontiguousarray(h_offsets, dtype=np.int64)
+    if type(h_offsets) is not np.ndarray or h_offsets.dtype != np.int64 or not h_offsets.flags.c_contiguous:
+        h_offsets = np.ascontiguousarray(h_offsets, dtype=np.int64)
     _check(lib().dnatok_encode_plan(handle, h_offsets.ctypes.data, n, ctypes.byref(opts),
                                     ctypes.byref(tot), ctypes.byref(mx)))
     return tot.value, mx.value
@@ -335,10 +336,11 @@ def dnatok_stream_destroy(handle) -> int:
 # ---- torch-facing helpers ----------------------------------------------------------
 
 def _stream_ptr(stream):
+    if stream is not None:
+        return stream.cuda_stream
     import torch
-    if stream is None:
-        stream = torch.cuda.current_stream()
-    return stream.cuda_stream
+    raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)  # 0.3 us; a Stream object takes 2.9
+    return raw(torch.cuda.current_device()) if raw else torch.cuda.current_stream().cuda_stream
 
 
 def _ptr(t):
@@ -384,7 +386,8 @@ def make_opts(add_cls_sep=False, layout=PACKED, pad_side=PAD_RIGHT, pad_to=0, of
 
 
 def plan(vocab: Vocab, h_offsets, add_cls_sep=False, variant=0):
-    h_offsets = np.ascontiguousarray(h_offsets, dtype=np.int64)
+    if type(h_offsets) is not np.ndarray or h_offsets.ndim != 1:
+        h_offsets = np.ascontiguousarray(h_offsets, dtype=np.int64)
     return dnatok_encode_plan(vocab.handle, h_offsets, len(h_offsets) - 1, make_opts(add_cls_sep, variant=variant))
 
 
@@ -417,7 +420,13 @@ def encode(vocab: Vocab, d_bytes, d_offsets, h_offsets=None, add_cls_sep=False, 
         cap = n * W
     else:
         W, cap = 0, total
-    if out is None:
+    whole = out is None and cap > 0 and vocab.kind != BPE  # the tensors are returned as they are made
+    if whole:
+        shape = (n, W) if layout == PADDED else (cap,)
+        ids = torch.empty(*shape, dtype=torch.int32, device=dev)
+        out_off = torch.empty(n + 1, dtype=torch.int64, device=dev)
+        mask = torch.empty(*shape, dtype=torch.int8, device=dev) if layout == PADDED else None
+    elif out is None:
         ids = torch.empty(max(cap, 1), dtype=torch.int32, device=dev)
         out_off = torch.empty(n + 1, dtype=torch.int64, device=dev)
         mask = torch.empty(max(cap, 1), dtype=torch.int8, device=dev) if layout == PADDED else None
@@ -426,6 +435,8 @@ def encode(vocab: Vocab, d_bytes, d_offsets, h_offsets=None, add_cls_sep=False, 
     opts = make_opts(add_cls_sep, layout, pad_side, W, variant=variant)
     dnatok_encode(vocab.handle, _ptr(d_bytes), d_bytes.numel(), _ptr(d_offsets), n, _ptr(ids), ids.numel(),
                   _ptr(out_off), _ptr(mask), opts, _stream_ptr(stream))
+    if whole:
+        return ids, out_off, mask
     if layout == PADDED:
         return ids[:cap].view(n, W) if n else ids[:0].view(0, W), out_off, mask[:cap].view(n, W) if n else mask[:0]
     if vocab.kind == BPE:
