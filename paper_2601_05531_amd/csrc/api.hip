@@ -100,6 +100,7 @@ void drop_workspace(hipStream_t stream) {
     if (ws) {
         if (ws->d_hdr) (void)hipFree(ws->d_hdr);
         if (ws->d_scratch) (void)hipFree(ws->d_scratch);
+        if (ws->d_decode) (void)hipFree(ws->d_decode);
         delete ws;
     }
     g_ws.erase(it);
@@ -149,10 +150,9 @@ int get_workspace(hipStream_t stream, int64_t tiles, Workspace **out) {
             DNATOK_HIP(hipFree(ws->d_hdr));
             ws->d_hdr = nullptr;
             ws->d_status = nullptr;
-            ws->d_decode = nullptr;
             ws->cap = 0;
         }
-        size_t bytes = 256 + ((size_t)cap * 2 + kDecodeWords) * sizeof(uint64_t);
+        size_t bytes = 256 + (size_t)cap * 2 * sizeof(uint64_t);
         void *p = nullptr;
         DNATOK_HIP(dev_alloc(&p, bytes));
         // zero on the workspace's own stream and wait: a plain hipMemset runs on
@@ -161,7 +161,6 @@ int get_workspace(hipStream_t stream, int64_t tiles, Workspace **out) {
         DNATOK_HIP(hipStreamSynchronize(stream));
         ws->d_hdr = static_cast<uint32_t *>(p);
         ws->d_status = reinterpret_cast<uint64_t *>(static_cast<uint8_t *>(p) + 256);
-        ws->d_decode = ws->d_status + 2 * cap;
         ws->cap = cap;
         ws->high_water = 0;
         if (err_keep) {
@@ -170,6 +169,19 @@ int get_workspace(hipStream_t stream, int64_t tiles, Workspace **out) {
         }
     }
     *out = ws;
+    return DNATOK_OK;
+}
+
+int ensure_decode(Workspace *ws) {
+    if (ws->d_decode || ws->fixed) return DNATOK_OK;
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(ws->stream, &st) != hipSuccess || st != hipStreamCaptureStatusNone) return DNATOK_OK;
+    DNATOK_HIP(hipStreamSynchronize(ws->stream));
+    void *p = nullptr;
+    DNATOK_HIP(dev_alloc(&p, kDecodeWords * sizeof(uint64_t)));
+    DNATOK_HIP(hipMemsetAsync(p, 0, kDecodeWords * sizeof(uint64_t), ws->stream));
+    DNATOK_HIP(hipStreamSynchronize(ws->stream));
+    ws->d_decode = static_cast<uint64_t *>(p);
     return DNATOK_OK;
 }
 

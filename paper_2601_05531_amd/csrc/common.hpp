@@ -143,7 +143,7 @@ struct Workspace {
     uint64_t *d_status = nullptr;  // 2 * cap words (parity 0 then parity 1)
     int64_t cap = 0;               // tiles
     int64_t high_water = 0;        // tiles that may hold non-zero status
-    uint64_t *d_decode = nullptr;  // kDecodeWords words of the decode's scan over tiles (fixed: none)
+    uint64_t *d_decode = nullptr;  // kDecodeWords words of the decode's scan over tiles, from the first decode on
     uint8_t *d_scratch = nullptr;  // general scratch for multi-pass kernels (BPE)
     int64_t scratch_bytes = 0;
     bool fixed = false;            // lives in the library's fixed device array: never grows
@@ -158,6 +158,10 @@ int get_workspace(hipStream_t stream, int64_t tiles, Workspace **out);
 // Ensure the workspace scratch holds at least `bytes` bytes (a fixed
 // workspace: EBUDGET when it does not).
 int ensure_scratch(Workspace *ws, int64_t bytes);
+// The decode's words, zeroed, unless the workspace is fixed or the stream is
+// capturing (d_decode then stays as it is, and the decode takes its words from
+// the scratch).
+int ensure_decode(Workspace *ws);
 // Routes the calling thread's launches to `ws` until the scope ends.
 class FixedWorkspaceScope {
   public:

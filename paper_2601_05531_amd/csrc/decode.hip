@@ -598,6 +598,10 @@ int launch_fixed(DecodeArgs a, Workspace *ws, hipStream_t stream) {
     if (a.ntiles >= (1ll << 31)) return set_error(DNATOK_EINVAL, "too many ids for one decode");
     a.rows_per_id = a.n_ids > 0 ? (double)a.n / (double)a.n_ids : 0.0;
     a.codes = 1u << (2 * K);
+    if (a.ntiles <= kDecodeTiles) {
+        int rc = ensure_decode(ws);
+        if (rc) return rc;
+    }
     ScanState st = scan_state(ws->d_decode, kDecodeTiles);
     if (!ws->d_decode || a.ntiles > kDecodeTiles) {
         const int64_t nw = scan_words(a.ntiles);
