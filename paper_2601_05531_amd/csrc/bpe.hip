@@ -132,7 +132,7 @@ int build_bpe_tables(dnatok_vocab *v) {
     DNATOK_HIP(dev_alloc(&p, sizeof(int64_t) * (size_t)V));
     t.d_tok_off = static_cast<int64_t *>(p);
     DNATOK_HIP(hipMemcpy(t.d_tok_off, off.data(), sizeof(int64_t) * (size_t)V, hipMemcpyHostToDevice));
-    DNATOK_HIP(dev_alloc(&p, chars.size()));
+    DNATOK_HIP(dev_alloc(&p, chars.size() + 16));  // the decode reads 16 bytes from a token's first on
     t.d_tok_chars = static_cast<uint8_t *>(p);
     DNATOK_HIP(hipMemcpy(t.d_tok_chars, chars.data(), chars.size(), hipMemcpyHostToDevice));
     return build_bpe_chunk_tables(v);

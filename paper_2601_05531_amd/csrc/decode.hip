@@ -12,10 +12,8 @@
 // device-wide counter serializes at about 12 ns per ticket, which at
 // thousands of tiles outweighs the decode).
 //
-// Single-nucleotide and k-mer ids (K bytes or none each) take one launch
-// (k_decode_fixed). BPE ids (tokens of any length) take two: a row pass, then
-// the tiles with a decoupled look-back (Merrill and Garland's single-pass
-// prefix scan).
+// Single-nucleotide and k-mer ids are K bytes or none each (k_decode_fixed),
+// BPE ids tokens of any length (k_decode_bpe); both take one launch.
 #include "common.hpp"
 #include "device.hpp"
 
@@ -24,9 +22,7 @@ namespace dnatok {
 namespace {
 
 constexpr int NT = 256;
-constexpr int TPT = 16;  // BPE tokens per thread (fewer, smaller tiles measured slower)
-constexpr int TT = NT * TPT;
-constexpr int kMaxStage = 32768;  // most bytes of one tile's output staged in LDS
+constexpr int kMaxStage = 32768;  // most bytes of a BPE tile's output staged in LDS
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef int32_t ids4 __attribute__((ext_vector_type(4), aligned(4)));
 
@@ -46,12 +42,9 @@ struct DecodeArgs {
     const uint8_t *tok_chars;
     int64_t ntiles;
     int32_t stage;       // bytes the LDS stage holds (a tile with more output writes its tokens directly)
-    uint64_t *status;    // BPE: tile status words of the look-back (ntiles), cleared by the row pass
-    int64_t *first_row;  // BPE: first row starting at or after each tile's first position (ntiles + 1)
     uint32_t *err_hdr;
-    // fixed widths
     double rows_per_id;
-    uint32_t codes;         // 4^k
+    uint32_t codes;      // 4^k
 };
 
 __device__ __forceinline__ bool is_silent(int32_t id) {
@@ -88,86 +81,6 @@ __device__ __forceinline__ void write_token(const DecodeArgs &a, int32_t id, int
     else err |= DNATOK_DERR_CAPACITY;
 }
 
-// The bytes of one id written to LDS at p (no bounds: the tile's staged
-// output fits the stage).
-__device__ __forceinline__ void stage_token(const DecodeArgs &a, int32_t id, uint8_t *p) {
-    if (is_silent(id)) return;
-    if (id >= 10 && id < a.vocab) {
-        const int64_t L = a.tok_len[id], o = a.tok_off[id];
-#pragma unroll 1
-        for (int64_t j = 0; j < L; ++j) p[j] = a.tok_chars[o + j];
-        return;
-    }
-    p[0] = single_letter(id);
-}
-
-// The ids of tile t this thread holds (TPT consecutive positions; ids
-// outside the rows read as PAD, which decodes to nothing). Every load is
-// unconditional, so a thread's loads go out together: a tile inside the rows
-// reads its TPT ids as 16-byte vectors, other tiles read clamped positions
-// and select.
-__device__ __forceinline__ int64_t load_tile_ids(const DecodeArgs &a, int64_t t, int64_t first, int64_t last,
-                                                 int32_t (&idv)[TPT]) {
-    const int64_t p0 = t * TT + (int64_t)threadIdx.x * TPT;
-    const bool inside = t * TT >= first && (t + 1) * TT <= last && (t + 1) * TT <= a.n_ids &&
-                        (reinterpret_cast<uintptr_t>(a.ids) & 15) == 0;  // uniform over the block
-    if (inside) {
-        const int4 *q = reinterpret_cast<const int4 *>(a.ids + p0);
-#pragma unroll
-        for (int j = 0; j < TPT; j += 4) {
-            const int4 v = q[j / 4];
-            idv[j] = v.x;
-            idv[j + 1] = v.y;
-            idv[j + 2] = v.z;
-            idv[j + 3] = v.w;
-        }
-    } else if (a.n_ids > 0) {
-        int32_t v[TPT];
-#pragma unroll
-        for (int j = 0; j < TPT; ++j) {
-            const int64_t p = p0 + j;
-            const bool live = p >= first && p < last && p < a.n_ids && p >= 0;
-            v[j] = a.ids[live ? p : 0];
-        }
-#pragma unroll
-        for (int j = 0; j < TPT; ++j) {
-            const int64_t p = p0 + j;
-            const bool live = p >= first && p < last && p < a.n_ids && p >= 0;
-            idv[j] = live ? v[j] : DNATOK_ID_PAD;
-        }
-    } else {
-#pragma unroll
-        for (int j = 0; j < TPT; ++j) idv[j] = DNATOK_ID_PAD;
-    }
-    int32_t mine = 0;  // a thread's 16 tokens of at most 2^20 bases each: 32 bits
-#pragma unroll
-    for (int j = 0; j < TPT; ++j) mine += width_of(a, idv[j]);
-    return mine;
-}
-
-// BPE 1. The row pass: the first row of every tile, the offsets check, and the
-// tile status words cleared for the write pass. Row i is the first row at or
-// after position t * TT exactly for the tiles t with
-// floor(off[i-1] / TT) < t <= floor(off[i] / TT) (row n stands for the end:
-// every tile past the last row start). Bad offsets only raise the flag; the
-// tile range is clamped, and the write pass clamps what it reads.
-__global__ __launch_bounds__(NT) void k_decode_rows(DecodeArgs a) {
-    uint32_t err = 0;
-    const int64_t G = (int64_t)gridDim.x * NT;
-    for (int64_t i = (int64_t)blockIdx.x * NT + threadIdx.x; i <= a.n; i += G) {
-        const int64_t prev = (i == 0) ? -1 : a.offs[i - 1];
-        const int64_t cur = (i == a.n) ? -1 : a.offs[i];
-        if (i < a.n && (cur < 0 || (i + 1 <= a.n && a.offs[i + 1] < cur) || a.offs[i + 1] > a.n_ids))
-            err |= DNATOK_DERR_OFFSETS;
-        int64_t lo = (i == 0) ? 0 : (prev < 0 ? 0 : prev / TT + 1);
-        int64_t hi = (i == a.n) ? a.ntiles : (cur < 0 ? -1 : cur / TT);
-        if (hi > a.ntiles) hi = a.ntiles;
-        for (int64_t t = lo; t <= hi; ++t) a.first_row[t] = i;
-    }
-    for (int64_t t = (int64_t)blockIdx.x * NT + threadIdx.x; t < a.ntiles; t += G) a.status[t] = 0;
-    if (err) dev::raise_error(a.err_hdr, err);
-}
-
 // The staged output of a tile (agg bytes from stage byte 0) to out + base:
 // output byte base + b is stage byte b, for b below the capacity (past it:
 // the flag); the output's 16-byte units from out + base - ph on, each read
@@ -199,100 +112,7 @@ __device__ __forceinline__ void store_stage(const DecodeArgs &a, const uint8_t *
     }
 }
 
-// BPE 2. One workgroup per tile: the tile's ids are read once; their byte total is published for later tiles before the
-// look-back, which wave 0 runs while the other waves stage the tile's bytes
-// in LDS. Once the output position is known, the block writes the output's
-// 16-byte units (each read from the stage realigned to the output's phase;
-// partial first and last units byte by byte), up to the capacity (past it:
-// the flag); a tile whose output exceeds the stage writes its tokens
-// directly. Rows starting in the tile get their output offsets; the last
-// tile writes the total.
-__global__ __launch_bounds__(NT) void k_decode_write(DecodeArgs a) {
-    extern __shared__ __align__(16) uint8_t s_out[];
-    __shared__ int64_t s_tpre[NT + 1];  // in-tile bytes before each thread's first position (and the total)
-    __shared__ int64_t s_tmp[NT / dev::kWave + 1];
-    __shared__ int64_t s_ia, s_ib, s_base;
-    const int tid = threadIdx.x;
-    const int64_t t = blockIdx.x;
-    const int64_t P0 = t * TT;
-    // the tile's rows go out with its ids (neither depends on the other)
-    int64_t ia = 0, ib = 0;
-    if (tid == 0) {
-        ia = a.first_row[t];
-        ib = (t == a.ntiles - 1) ? a.n : a.first_row[t + 1];
-    }
-    const int64_t first = (a.n > 0) ? a.offs[0] : 0;
-    const int64_t last = (a.n > 0) ? a.offs[a.n] : 0;
-    int32_t idv[TPT];
-    const int64_t mine = load_tile_ids(a, t, first, last, idv);
-    int64_t agg;
-    const int64_t pre = dev::block_excl_scan<NT>(mine, s_tmp, &agg);
-    if (tid < dev::kWave) {
-        if (tid == 0) dev::publish_aggregate(a.status, t, agg);
-        const int64_t excl = dev::wave_lookback(a.status, t, agg, a.err_hdr);
-        if (tid == 0) {
-            // rows starting in the tile (clamped: bad offsets leave the
-            // table unchecked, and they raise the flag in the row pass)
-            ia = ia < 0 ? 0 : (ia > a.n ? a.n : ia);
-            ib = ib < ia ? ia : (ib > a.n ? a.n : ib);
-            s_ia = ia;
-            s_ib = ib;
-            s_base = excl;
-        }
-    }
-    s_tpre[tid] = pre;
-    if (tid == NT - 1) s_tpre[NT] = pre + mine;
-    // The bytes go to LDS from stage offset 0 while wave 0 still waits on
-    // the look-back (their output position matters only to the stores).
-    const bool staged = agg <= a.stage;
-    if (staged) {
-        // in-tile positions fit 32 bits (the stage is at most 32 KiB)
-        uint32_t pos = (uint32_t)pre;
-#pragma unroll
-        for (int j = 0; j < TPT; ++j) {
-            stage_token(a, idv[j], s_out + pos);
-            pos += (uint32_t)width_of(a, idv[j]);
-        }
-    }
-    __syncthreads();
-    const int64_t base = s_base;
-    uint32_t err = 0;
-    if (staged) {
-        store_stage(a, s_out, base, agg, err);
-    } else {
-        // rare (output over the stage): the ids again, one at a time from
-        // the cache, written straight to the output
-        int64_t pos = base + pre;
-        const int64_t p0 = t * TT + (int64_t)tid * TPT;
-#pragma unroll 1
-        for (int j = 0; j < TPT; ++j) {
-            const int64_t q = p0 + j;
-            const bool live = q >= first && q < last && q < a.n_ids;
-            const int32_t id = live ? a.ids[q] : DNATOK_ID_PAD;
-            write_token(a, id, pos, err);
-            pos += width_of(a, id);
-        }
-    }
-    // rows starting in the tile: the bytes before their first position are
-    // the owning thread's prefix plus its ids before that position (read
-    // again from the cache; a tile holds a few row starts)
-    for (int64_t i = s_ia + tid; i < s_ib; i += NT) {
-        int64_t rel = a.offs[i] - P0;
-        rel = rel < 0 ? 0 : (rel > TT ? TT : rel);
-        const int th = (int)(rel / TPT);
-        int64_t sum = s_tpre[th];
-        for (int64_t q = P0 + (int64_t)th * TPT; q < P0 + rel; ++q) {
-            const bool live = q >= first && q < last && q < a.n_ids;
-            sum += width_of(a, live ? a.ids[q] : DNATOK_ID_PAD);
-        }
-        a.out_offs[i] = base + sum;
-    }
-    if (t == a.ntiles - 1 && tid == 0) a.out_offs[a.n] = base + agg;
-    if (err) dev::raise_error(a.err_hdr, err);
-}
-
-
-// State of k_decode_fixed's scan over tiles: per tile its output bytes, per
+// State of the scan over tiles: per tile its output bytes, per
 // group of 64 tiles and per super of 64 groups their sum, each word complete
 // when bit 63 is set. The last tile of a group adds its group up as soon as
 // the group's tiles have published, so a group hangs on no look-back, and the
@@ -351,6 +171,104 @@ __device__ __forceinline__ uint32_t check_rows(const DecodeArgs &a, int64_t r) {
     return o0 < 0 || o1 < o0 || o1 > a.n_ids ? DNATOK_DERR_OFFSETS : 0;
 }
 
+// The rows past those that tiles check.
+__device__ __forceinline__ void check_rest(const DecodeArgs &a, int64_t block) {
+    const int64_t r0 = a.ntiles * kCheckRows + block * kCheckBlock;
+    uint32_t err = 0;
+    for (int64_t r = r0 + threadIdx.x; r < r0 + kCheckBlock; r += NT) err |= check_rows(a, r);
+    if (err) dev::raise_error(a.err_hdr, err);
+}
+
+// The half of the state that this launch works on, and what is left to clear
+// in the other.
+struct ScanView {
+    uint64_t half;
+    int64_t left;
+    uint64_t *tile, *group, *super, *other;
+};
+__device__ __forceinline__ ScanView scan_view(const ScanState &st) {
+    ScanView v;
+    v.half = dev::ld_relaxed(st.head) & 1u;
+    v.left = (int64_t)dev::ld_relaxed(st.head + 2 - v.half);
+    v.tile = v.half ? st.half[1] : st.half[0];
+    v.other = v.half ? st.half[0] : st.half[1];
+    v.group = v.tile + st.tiles;
+    v.super = v.group + st.groups;
+    return v;
+}
+// Publishes tile t's bytes (one thread of the first wave) and clears a share
+// of the other half (all threads).
+__device__ __forceinline__ void publish_tile(const ScanState &st, const ScanView &v, int64_t t, int64_t ntiles,
+                                             int64_t agg) {
+    if (threadIdx.x == 0) dev::st_relaxed(v.tile + t, kComplete | (uint64_t)agg);
+    for (int64_t i = t * NT + threadIdx.x; i < v.left; i += ntiles * NT) {
+        dev::st_relaxed(v.other + i, 0);
+        if (i % 64 == 0) dev::st_relaxed(v.other + st.tiles + i / 64, 0);
+        if (i % 4096 == 0) dev::st_relaxed(v.other + st.tiles + st.groups + i / 4096, 0);
+    }
+}
+// Bytes before tile t, by one wave. Nearest words first: the older ones are
+// then there already.
+__device__ __forceinline__ int64_t tile_position(const ScanView &v, int64_t t, int64_t agg, uint32_t *hdr) {
+    const int64_t g = t / 64, sp = g / 64;
+    const bool one = (threadIdx.x & (dev::kWave - 1)) == 0;
+    int64_t sum = sum_complete(v.tile, g * 64, t, hdr);
+    if (t % 64 == 63 && one) dev::st_relaxed(v.group + g, kComplete | (uint64_t)(sum + agg));
+    sum += sum_complete(v.group, sp * 64, g, hdr);
+    if (t % 4096 == 4095 && one) dev::st_relaxed(v.super + sp, kComplete | (uint64_t)(sum + agg));
+    return sum + sum_complete(v.super, 0, sp, hdr);
+}
+// The last tile ends the offsets and hands the other half to the next launch
+// (one thread).
+__device__ __forceinline__ void finish_tiles(const DecodeArgs &a, const ScanState &st, const ScanView &v,
+                                             int64_t total) {
+    a.out_offs[a.n] = total;
+    dev::st_relaxed(st.head + 1 + v.half, (uint64_t)a.ntiles);
+    dev::st_relaxed(st.head, v.half ^ 1u);
+}
+
+// The rows around a tile: the offsets of 64 from g0 on (asked for early by
+// one wave, g0 being where the tile would start if rows were equally long),
+// and the first row that starts in the tile.
+struct TileRows {
+    int64_t po[dev::kWave];
+    int64_t g0, ia;
+};
+__device__ __forceinline__ int64_t probe_rows(const DecodeArgs &a, int64_t P0, int64_t *g0) {
+    int64_t g = (int64_t)((double)P0 * a.rows_per_id) - dev::kWave / 2;
+    if (g + dev::kWave > a.n) g = a.n - dev::kWave;
+    if (g < 0) g = 0;
+    *g0 = g;
+    return a.offs[min(g + (int64_t)(threadIdx.x & (dev::kWave - 1)), (int64_t)a.n)];
+}
+__device__ __forceinline__ void find_rows(const DecodeArgs &a, int64_t P0, int64_t g0, int64_t po, TileRows &rows) {
+    const int lane = threadIdx.x & (dev::kWave - 1);
+    const int64_t n = a.n;
+    auto pred = [&](int64_t r) { return a.offs[r] >= P0; };
+    const uint64_t hit = __ballot(g0 + lane < n ? po >= P0 : true);
+    int64_t ia;
+    if ((hit & 1ull) && g0 > 0) ia = dev::wave_lower_bound(0, g0, pred);
+    else if (hit == 0) ia = dev::wave_lower_bound(g0 + dev::kWave, n, pred);
+    else ia = g0 + __builtin_ctzll(hit);
+    rows.po[lane] = po;
+    if (lane == 0) {
+        rows.ia = min(ia, n);
+        rows.g0 = g0;
+    }
+}
+// Output offsets of the rows that start in [P0, P0 + tt) (the last tile: from
+// P0 on); bytes_at(rel): the tile's bytes before its position rel.
+template <class F>
+__device__ __forceinline__ void put_rows(const DecodeArgs &a, const TileRows &rows, int64_t P0, int64_t tt, bool last,
+                                         int64_t base, F bytes_at) {
+    const int64_t w0 = rows.g0;
+    for (int64_t i = rows.ia + threadIdx.x; i < a.n; i += NT) {
+        const int64_t o = i >= w0 && i - w0 < dev::kWave ? rows.po[i - w0] : a.offs[i];
+        if (o >= P0 + tt && !last) break;
+        a.out_offs[i] = base + bytes_at((int32_t)min(max(o - P0, (int64_t)0), tt));
+    }
+}
+
 // The K letters of known k-mer code v, first letter in the low byte of w[0];
 // bytes past the K-th are zero. known false: K letters N.
 template <int K>
@@ -386,18 +304,16 @@ __global__ __launch_bounds__(NT) void k_decode_fixed(DecodeArgs a, ScanState st)
     __shared__ uint32_t s_wave[NW];        // non-silent ids of a wave
     __shared__ uint32_t s_pre[NW * U];     // non-silent ids of the wave before a slice
     __shared__ uint64_t s_silent[NW * U][4];
-    __shared__ int64_t s_po[dev::kWave];   // offsets of the rows from s_g0 on
-    __shared__ int64_t s_ia, s_g0, s_base;
+    __shared__ TileRows s_rows;
+    __shared__ int64_t s_base;
     const int tid = threadIdx.x, lane = tid & (dev::kWave - 1);
     const int w = __builtin_amdgcn_readfirstlane(tid / dev::kWave);
     const int64_t t = blockIdx.x;
     const int64_t P0 = t * FT;
     const int64_t n = a.n;
     uint32_t err = 0;
-    if (t >= a.ntiles) {  // rows that no tile checks
-        for (int64_t r = a.ntiles * kCheckRows + (t - a.ntiles) * kCheckBlock + tid; r < a.ntiles * kCheckRows + (t - a.ntiles + 1) * kCheckBlock; r += NT)
-            err |= check_rows(a, r);
-        if (err) dev::raise_error(a.err_hdr, err);
+    if (t >= a.ntiles) {
+        check_rest(a, t - a.ntiles);
         return;
     }
 
@@ -416,17 +332,11 @@ __global__ __launch_bounds__(NT) void k_decode_fixed(DecodeArgs a, ScanState st)
             }
     }
     const int64_t first = n > 0 ? a.offs[0] : 0, last = n > 0 ? a.offs[n] : 0;
-    const uint64_t half = dev::ld_relaxed(st.head) & 1u;
-    const int64_t left = (int64_t)dev::ld_relaxed(st.head + 2 - half);  // tiles left in the other half
-    uint64_t *tile_word = half ? st.half[1] : st.half[0], *other = half ? st.half[0] : st.half[1];
-    uint64_t *group_word = tile_word + st.tiles, *super_word = group_word + st.groups;
-    int64_t g0 = 0, po = 0;  // 64 rows around the one the tile would start in if rows were equally long
+    const ScanView v = scan_view(st);
+    int64_t g0 = 0, po = 0;
     if (w == NW - 1) {
         err |= check_rows(a, t * kCheckRows + lane);
-        g0 = (int64_t)((double)P0 * a.rows_per_id) - dev::kWave / 2;
-        if (g0 + dev::kWave > n) g0 = n - dev::kWave;
-        if (g0 < 0) g0 = 0;
-        po = a.offs[min(g0 + lane, n)];
+        po = probe_rows(a, P0, &g0);
     }
     if (P0 < first || P0 + FT > last) {  // ids outside the rows decode to nothing
 #pragma unroll
@@ -467,26 +377,9 @@ __global__ __launch_bounds__(NT) void k_decode_fixed(DecodeArgs a, ScanState st)
         before += i < w ? s_wave[i] : 0;
         total += s_wave[i];
     }
-    const int64_t agg = (int64_t)K * total, g = t / 64, sp = g / 64;
-    if (w == 0 && lane == 0) dev::st_relaxed(tile_word + t, kComplete | (uint64_t)agg);
-    for (int64_t i = t * NT + tid; i < left; i += a.ntiles * NT) {
-        dev::st_relaxed(other + i, 0);
-        if (i % 64 == 0) dev::st_relaxed(other + st.tiles + i / 64, 0);
-        if (i % 4096 == 0) dev::st_relaxed(other + st.tiles + st.groups + i / 4096, 0);
-    }
-    if (w == NW - 1) {  // the first row that starts in the tile
-        auto pred = [&](int64_t r) { return a.offs[r] >= P0; };
-        const uint64_t hit = __ballot(g0 + lane < n ? po >= P0 : true);
-        int64_t ia;
-        if ((hit & 1ull) && g0 > 0) ia = dev::wave_lower_bound(0, g0, pred);
-        else if (hit == 0) ia = dev::wave_lower_bound(g0 + dev::kWave, n, pred);
-        else ia = g0 + __builtin_ctzll(hit);
-        s_po[lane] = po;
-        if (lane == 0) {
-            s_ia = min(ia, n);
-            s_g0 = g0;
-        }
-    }
+    const int64_t agg = (int64_t)K * total;
+    publish_tile(st, v, t, a.ntiles, agg);
+    if (w == NW - 1) find_rows(a, P0, g0, po, s_rows);
     // the bytes to LDS
 #pragma unroll
     for (int s = 0; s < U; ++s) {
@@ -536,43 +429,164 @@ __global__ __launch_bounds__(NT) void k_decode_fixed(DecodeArgs a, ScanState st)
         }
     }
     if (w == 0) {
-        // nearest first: the older words are then there already
-        int64_t sum = sum_complete(tile_word, g * 64, t, a.err_hdr);
-        if (t % 64 == 63 && lane == 0) dev::st_relaxed(group_word + g, kComplete | (uint64_t)(sum + agg));
-        const int64_t in_super = sum_complete(group_word, sp * 64, g, a.err_hdr);
-        sum += in_super;
-        if (t % 4096 == 4095 && lane == 0) dev::st_relaxed(super_word + sp, kComplete | (uint64_t)(sum + agg));
-        sum += sum_complete(super_word, 0, sp, a.err_hdr);
+        const int64_t sum = tile_position(v, t, agg, a.err_hdr);
         if (lane == 0) s_base = sum;
     }
     __syncthreads();
     const int64_t base = s_base;
     store_stage(a, s_out, base, agg, err);
     // rows starting in the tile: K bytes per non-silent id before their first position
-    const int64_t w0 = s_g0;
-    for (int64_t i = s_ia + tid; i < n; i += NT) {
-        const int64_t o = i >= w0 && i - w0 < dev::kWave ? s_po[i - w0] : a.offs[i];
-        if (o >= P0 + FT && t < a.ntiles - 1) break;
-        const int32_t rel = (int32_t)min(max(o - P0, (int64_t)0), (int64_t)FT);
+    put_rows(a, s_rows, P0, FT, t == a.ntiles - 1, base, [&](int32_t rel) {
         uint32_t c = total;
         if (rel < FT) {
             const int sl = rel / 256, l = (rel % 256) / 4, q0 = rel % 4;
             c = s_pre[sl] + (uint32_t)(rel % 256);
-            for (int i2 = 0; i2 < sl / U; ++i2) c += s_wave[i2];
+            for (int i = 0; i < sl / U; ++i) c += s_wave[i];
             for (int q = 0; q < 4; ++q) {
                 const uint64_t m = s_silent[sl][q];
                 c -= (uint32_t)__popcll(m & ((1ull << l) - 1ull));
                 if (q < q0) c -= (uint32_t)(m >> l) & 1u;
             }
         }
-        a.out_offs[i] = base + (int64_t)K * c;
-    }
+        return (int64_t)K * c;
+    });
     if (err) dev::raise_error(a.err_hdr, err);
-    if (t == a.ntiles - 1 && tid == 0) {
-        a.out_offs[n] = base + agg;
-        dev::st_relaxed(st.head + 1 + half, (uint64_t)a.ntiles);
-        dev::st_relaxed(st.head, half ^ 1u);
+    if (t == a.ntiles - 1 && tid == 0) finish_tiles(a, st, v, base + agg);
+}
+
+// The first L (up to 16) bytes of v to p.
+__device__ __forceinline__ void put_bytes(uint8_t *p, const u32x4 &v, int32_t L) {
+#pragma unroll
+    for (int w = 0; w < 4; ++w) {
+        const int32_t r = L - 4 * w;
+        const uint32_t x = v[w];
+        if (r >= 4) {
+            __builtin_memcpy(p + 4 * w, &x, 4);
+        } else if (r > 0) {
+            if (r >= 2) __builtin_memcpy(p + 4 * w, &x, 2);
+            if (r & 1) p[4 * w + r - 1] = (uint8_t)(x >> (8 * (r - 1)));
+        }
     }
+}
+
+// BPE ids, TPT consecutive ones per thread: their lengths and the first 16
+// bases of each are asked for together (three dependent loads a tile, whatever
+// its tokens; a loop of byte loads per token took 0.5 us a byte), then staged.
+// A tile whose output exceeds the stage writes its tokens to the output one by
+// one. Bound by that chain of loads and the wait for the position: 968,000
+// ids (5.5 MB of bases) 30.6 -> 14.8 us, 174,000 28.5 -> 9.7, 184 18.7 -> 7.4;
+// a row pass, a chain of prefixes and the byte loops before.
+template <int TPT>
+__global__ __launch_bounds__(NT) void k_decode_bpe(DecodeArgs a, ScanState st) {
+    constexpr int FT = NT * TPT;
+    extern __shared__ __align__(16) uint8_t s_out[];
+    __shared__ int64_t s_tpre[NT + 1];  // in-tile bytes before each thread's first position (and the total)
+    __shared__ int64_t s_tmp[NT / dev::kWave + 1];
+    __shared__ TileRows s_rows;
+    __shared__ int64_t s_base;
+    const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid / dev::kWave);
+    const int64_t t = blockIdx.x;
+    const int64_t P0 = t * FT, p0 = P0 + tid * TPT;
+    const int64_t n = a.n;
+    uint32_t err = 0;
+    if (t >= a.ntiles) {
+        check_rest(a, t - a.ntiles);
+        return;
+    }
+    int32_t id[TPT];
+    if (P0 + FT <= a.n_ids) {
+#pragma unroll
+        for (int j = 0; j < TPT; j += 4) {
+            const ids4 x = *reinterpret_cast<const ids4 *>(a.ids + p0 + j);
+#pragma unroll
+            for (int q = 0; q < 4; ++q) id[j + q] = x[q];
+        }
+    } else {
+#pragma unroll
+        for (int j = 0; j < TPT; ++j) id[j] = p0 + j < a.n_ids ? a.ids[p0 + j] : DNATOK_ID_PAD;
+    }
+    const int64_t first = n > 0 ? a.offs[0] : 0, last = n > 0 ? a.offs[n] : 0;
+    const ScanView v = scan_view(st);
+    int64_t g0 = 0, po = 0;
+    if (w == NT / dev::kWave - 1) {
+        err |= check_rows(a, t * kCheckRows + (tid & (dev::kWave - 1)));
+        po = probe_rows(a, P0, &g0);
+    }
+    auto merged = [&](int32_t x) { return x >= 10 && x < a.vocab; };
+    int32_t len[TPT];
+    int64_t off[TPT];
+#pragma unroll
+    for (int j = 0; j < TPT; ++j) {
+        if (p0 + j < first || p0 + j >= last) id[j] = DNATOK_ID_PAD;  // ids outside the rows decode to nothing
+        len[j] = is_silent(id[j]) ? 0 : 1;
+        off[j] = 0;
+        if (merged(id[j])) {
+            len[j] = a.tok_len[id[j]];
+            off[j] = a.tok_off[id[j]];
+        }
+    }
+    int64_t mine = 0;
+#pragma unroll
+    for (int j = 0; j < TPT; ++j) mine += len[j];
+    int64_t agg;
+    const int64_t pre = dev::block_excl_scan<NT>(mine, s_tmp, &agg);
+    publish_tile(st, v, t, a.ntiles, agg);
+    if (w == NT / dev::kWave - 1) find_rows(a, P0, g0, po, s_rows);
+    s_tpre[tid] = pre;
+    if (tid == NT - 1) s_tpre[NT] = pre + mine;
+    const bool staged = agg <= a.stage;
+    if (staged) {
+        uint32_t pos = (uint32_t)pre;  // the stage holds at most 32 KiB
+#pragma unroll
+        for (int j0 = 0; j0 < TPT; j0 += 4) {
+            u32x4 x[4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                x[j] = u32x4{single_letter(id[j0 + j]), 0, 0, 0};
+                if (merged(id[j0 + j])) __builtin_memcpy(&x[j], a.tok_chars + off[j0 + j], 16);
+            }
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const int32_t L = len[j0 + j];
+                put_bytes(s_out + pos, x[j], min(L, 16));
+                for (int32_t b = 16; b < L; b += 16) {
+                    u32x4 y;
+                    __builtin_memcpy(&y, a.tok_chars + off[j0 + j] + b, 16);
+                    put_bytes(s_out + pos + b, y, min(L - b, 16));
+                }
+                pos += (uint32_t)L;
+            }
+        }
+    }
+    if (w == 0) {
+        const int64_t sum = tile_position(v, t, agg, a.err_hdr);
+        if (tid == 0) s_base = sum;
+    }
+    __syncthreads();
+    const int64_t base = s_base;
+    if (staged) {
+        store_stage(a, s_out, base, agg, err);
+    } else {
+        int64_t pos = base + pre;
+#pragma unroll
+        for (int j = 0; j < TPT; ++j) {
+            write_token(a, id[j], pos, err);
+            pos += len[j];
+        }
+    }
+    // a row's bytes before its first position: the owning thread's prefix and
+    // its ids before that position (read again from the cache)
+    put_rows(a, s_rows, P0, FT, t == a.ntiles - 1, base, [&](int32_t rel) {
+        const int th = rel / TPT;
+        int64_t sum = s_tpre[th];
+        for (int64_t q = P0 + (int64_t)th * TPT; q < P0 + rel; ++q) {
+            const bool live = q >= first && q < last && q < a.n_ids;
+            sum += width_of(a, live ? a.ids[q] : DNATOK_ID_PAD);
+        }
+        return sum;
+    });
+    if (err) dev::raise_error(a.err_hdr, err);
+    if (t == a.ntiles - 1 && tid == 0) finish_tiles(a, st, v, base + agg);
 }
 
 static_assert(kDecodeWords == kHeadWords + 2 * (kDecodeTiles + kDecodeTiles / 64 + kDecodeTiles / 4096), "the workspace's words");
@@ -580,6 +594,30 @@ static_assert(kDecodeWords == kHeadWords + 2 * (kDecodeTiles + kDecodeTiles / 64
 __global__ void k_clear_words(uint64_t *p, int64_t n) {
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
         p[i] = 0;
+}
+
+// Tiles of tt ids: their count, the scan's state and the launch's grid.
+int plan_tiles(DecodeArgs &a, int64_t tt, Workspace *ws, hipStream_t stream, ScanState *st, dim3 *grid) {
+    a.ntiles = a.n_ids / tt + 1;
+    if (a.ntiles >= (1ll << 31)) return set_error(DNATOK_EINVAL, "too many ids for one decode");
+    a.rows_per_id = a.n_ids > 0 ? (double)a.n / (double)a.n_ids : 0.0;
+    if (a.ntiles <= kDecodeTiles) {
+        int rc = ensure_decode(ws);
+        if (rc) return rc;
+    }
+    *st = scan_state(ws->d_decode, kDecodeTiles);
+    if (!ws->d_decode || a.ntiles > kDecodeTiles) {
+        const int64_t nw = scan_words(a.ntiles);
+        int rc = ensure_scratch(ws, 8 * nw);
+        if (rc) return rc;
+        *st = scan_state(reinterpret_cast<uint64_t *>(ws->d_scratch), a.ntiles);
+        hipLaunchKernelGGL(k_clear_words, dim3((unsigned)std::min<int64_t>((nw + 255) / 256, 1024)), dim3(256), 0, stream,
+                           st->head, nw);
+        DNATOK_HIP(hipGetLastError());
+    }
+    const int64_t unchecked = std::max<int64_t>(0, a.n - a.ntiles * kCheckRows);
+    *grid = dim3((unsigned)(a.ntiles + (unchecked + kCheckBlock - 1) / kCheckBlock));
+    return DNATOK_OK;
 }
 
 template <int K>
@@ -594,25 +632,12 @@ int launch_fixed(DecodeArgs a, Workspace *ws, hipStream_t stream) {
     static_assert(1024 * UMAX * K <= 49152, "three tiles' stages fit a CU");
     int U = 1;
     while (U < UMAX && a.n_ids > 1024 * (int64_t)U * (K == 1 ? 5 : 7) * device_cu_count()) U <<= 1;
-    a.ntiles = a.n_ids / (1024 * U) + 1;
-    if (a.ntiles >= (1ll << 31)) return set_error(DNATOK_EINVAL, "too many ids for one decode");
-    a.rows_per_id = a.n_ids > 0 ? (double)a.n / (double)a.n_ids : 0.0;
     a.codes = 1u << (2 * K);
-    if (a.ntiles <= kDecodeTiles) {
-        int rc = ensure_decode(ws);
-        if (rc) return rc;
-    }
-    ScanState st = scan_state(ws->d_decode, kDecodeTiles);
-    if (!ws->d_decode || a.ntiles > kDecodeTiles) {
-        const int64_t nw = scan_words(a.ntiles);
-        int rc = ensure_scratch(ws, 8 * nw);
-        if (rc) return rc;
-        st = scan_state(reinterpret_cast<uint64_t *>(ws->d_scratch), a.ntiles);
-        hipLaunchKernelGGL(k_clear_words, dim3((unsigned)std::min<int64_t>((nw + 255) / 256, 1024)), dim3(256), 0, stream, st.head, nw);
-        DNATOK_HIP(hipGetLastError());
-    }
-    const int64_t unchecked = std::max<int64_t>(0, a.n - a.ntiles * kCheckRows);
-    const dim3 grid((unsigned)(a.ntiles + (unchecked + kCheckBlock - 1) / kCheckBlock)), block(NT);
+    ScanState st;
+    dim3 grid;
+    int rc = plan_tiles(a, 1024 * U, ws, stream, &st, &grid);
+    if (rc) return rc;
+    const dim3 block(NT);
     const size_t dyn = (size_t)1024 * U * K + 16;  // a unit's realigning reads go up to 3 bytes past the data
     switch (U) {
     case 1: hipLaunchKernelGGL((k_decode_fixed<K, 1>), grid, block, dyn, stream, a, st); break;
@@ -666,20 +691,18 @@ int launch_decode(const dnatok_vocab *v, const int32_t *d_ids, int64_t n_ids, co
         default: return launch_fixed<15>(a, ws, stream);
         }
     }
-    a.ntiles = n_ids / TT + 1;
-    if (a.ntiles >= (1ll << 31)) return set_error(DNATOK_EINVAL, "too many ids for one decode");
-    // the stage holds a tile's output at the vocabulary's widest token
-    a.stage = (int32_t)std::min<int64_t>((int64_t)TT * std::max<int64_t>(v->max_token_bytes, 1), kMaxStage);
-    rc = ensure_scratch(ws, 16 * (a.ntiles + 1));
+    // the stage holds a tile's output at the vocabulary's widest token. Tiles
+    // of 1,024 ids while all of them fit the card at once, else of 4,096.
+    const bool small = n_ids <= 1024 * 7 * (int64_t)device_cu_count();
+    const int64_t tt = small ? 1024 : 4096;
+    a.stage = (int32_t)std::min<int64_t>(tt * std::max<int64_t>(v->max_token_bytes, 1), kMaxStage);
+    ScanState st;
+    dim3 grid;
+    rc = plan_tiles(a, tt, ws, stream, &st, &grid);
     if (rc) return rc;
-    a.status = reinterpret_cast<uint64_t *>(ws->d_scratch);
-    a.first_row = reinterpret_cast<int64_t *>(a.status + (a.ntiles + 1));
-    const int64_t rows_grid = std::min<int64_t>(((int64_t)n + 1 + NT - 1) / NT + 1, 4ll * device_cu_count());
-    hipLaunchKernelGGL(k_decode_rows, dim3((unsigned)std::max<int64_t>(rows_grid, 1)), dim3(NT), 0, stream, a);
-    DNATOK_HIP(hipGetLastError());
-    const dim3 grid((unsigned)a.ntiles), block(NT);
     const size_t dyn = (size_t)a.stage + 16;  // a unit's realigning reads go up to 3 bytes past the data
-    hipLaunchKernelGGL(k_decode_write, grid, block, dyn, stream, a);
+    if (small) hipLaunchKernelGGL(k_decode_bpe<4>, grid, dim3(NT), dyn, stream, a, st);
+    else hipLaunchKernelGGL(k_decode_bpe<16>, grid, dim3(NT), dyn, stream, a, st);
     DNATOK_HIP(hipGetLastError());
     return DNATOK_OK;
 }

@@ -1,5 +1,5 @@
-"""GPU parity of the fixed-width decode (single letters, k-mers) where its
-tiles can go wrong: every number of slices per wave, slices with and without
+"""GPU parity of the decode (single letters, k-mers, BPE) where its tiles
+can go wrong: every number of slices per wave, slices with and without
 silent ids, groups of 64 and supers of 4,096 tiles, ids outside the rows,
 misaligned ids and outputs, many rows in one tile, launches of different sizes
 one after another, the words of very long decodes, and captured launches."""
@@ -136,4 +136,43 @@ def test_capture_and_replay():
             assert np.array_equal(oo.cpu().numpy(), want_off)
             assert np.array_equal(out.cpu().numpy()[:len(want)], want)
     assert dt.sync_status(s) == 0
+    v.close()
+
+
+@pytest.mark.parametrize("longest", [2, 15, 16, 17, 48, 4096])
+def test_bpe_tokens_of_every_length(longest):
+    """Tokens around the 16 bases read at once; 4,096 bases: tiles whose
+    output exceeds the stage; both tile sizes, edges of a thread's ids."""
+    import torch
+    merges, at = [(5, 6)], {2: 10}  # AC, then each token one base longer, or twice as long
+    n = 2
+    while n < longest:
+        step = n if longest > 64 else 1
+        merges.append((at[n], at[n] if step == n and longest > 64 else 5 + n % 4))
+        n += step
+        at[n] = 10 + len(merges) - 1
+    merges = np.array(merges, np.int32)
+    v = dt.Vocab(dt.BPE, merges=merges)
+    rng = np.random.default_rng(longest)
+    for n_ids in (0, 1, 15, 16, 1023, 1024, 1025, 4097, 60_000) + ((2_100_000,) if longest < 48 else ()):
+        ids = rng.integers(5, 10 + len(merges), n_ids).astype(np.int32)
+        odd = rng.random(n_ids) < 0.02
+        ids[odd] = rng.integers(-2, 14 + len(merges), int(odd.sum()))
+        offs = np.sort(np.concatenate([[0], rng.integers(0, n_ids + 1, 1 + n_ids // 700), [n_ids]])).astype(np.int64)
+        if n_ids % 2:
+            offs[0], offs[-1] = min(2, offs[1]), max(n_ids - 3, offs[-2])
+        print("bpe decode longest=%d ids=%d rows=%d" % (longest, n_ids, len(offs) - 1), flush=True)
+        want, want_off = oracle.decode(oracle.BPE, ids, offs, merges=merges)
+        cap = int(want_off[-1])
+        for short in (0, 5):
+            room = max(cap - short, 0)
+            out = torch.full((cap + 32,), 7, dtype=torch.uint8, device="cuda")
+            oo = torch.empty(len(offs), dtype=torch.int64, device="cuda")
+            d = torch.from_numpy(np.append(ids, np.int32(0))).cuda()
+            dt.dnatok_decode(v.handle, d.data_ptr(), n_ids, torch.from_numpy(offs).cuda().data_ptr(), len(offs) - 1,
+                             out.data_ptr() + 3, room, oo.data_ptr(), None)
+            assert dt.sync_status() == (dt.DERR_CAPACITY if short and cap else 0)
+            got = out.cpu().numpy()
+            assert np.array_equal(got[3:3 + room], want[:room]) and np.all(got[3 + room:] == 7)
+            assert np.array_equal(oo.cpu().numpy(), want_off)
     v.close()
