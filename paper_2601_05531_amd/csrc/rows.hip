@@ -87,7 +87,7 @@ struct RowsArgs {
     int64_t ntiles;
     // workgroups before the tiles: row scans (nv * scan_units of them), pads,
     // rows past the first 64 of a tile, then idle
-    int32_t pads, extra, lead;
+    int32_t pads, lead;
     int32_t scan_units;
     int32_t self_scan;  // PACKED: each workgroup scans the row lengths itself
     uint32_t wave_lds;  // dynamic LDS bytes of a wave
