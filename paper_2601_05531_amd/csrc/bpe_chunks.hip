@@ -23,8 +23,12 @@
 // occurs in one of the two. So a lane may stop as soon as its tokens meet
 // those that the next lane holds, provided that lane does not give them up
 // again: a wave ends when all of its lanes have met or ended at the same
-// time, and the waves' own sequences are joined at the token across each
-// wave's last chunk end, which both hold (k_bpe_walk checks it). The
+// time. The waves' own sequences are joined at the token across each wave's
+// last chunk end. Both waves segment that chunk, the first one's last own lane
+// against a lane that ends at its own last base, the second one's first lane
+// against one that reads on, so the two may differ: the join stands if both
+// hold the same token there and the second wave's first lane has met its
+// second one, whose tokens are the ones kept (k_bpe_walk checks it). The
 // segmentations of a text from two starting points share a token after a few
 // (9 bases in the median, 28 at most over 6,249 cuts of the 4,096-merge
 // table's corpus), so a lane reads 64 bases of its own and as many of the
@@ -580,14 +584,16 @@ __global__ __launch_bounds__(64 * kMaxWavesPerGroup) void k_bpe_chunks(ChunkArgs
         const uint64_t below = (1ull << from) - 1;
         const uint64_t prev_hi = from_prev(own.hi);
         const Bits t{(own.lo & ~below) | (prev_hi & below), own.hi};
-        // the token across a chunk end, for the next wave to compare
+        // the token across a chunk end, for k_bpe_walk to compare. Lane 0 has
+        // one only if its tokens go on in lane 1's: lane 1 keeps tokens that
+        // start at its own chunk edge otherwise.
         if (lane == kLead - 1 || lane == 62) {
             const uint32_t side = lane == 62 ? 1u : 0u;
             uint32_t token = 0;
             if (next_same)
-                token = t.lo && t.hi ? 0x10000u | ((63u - (uint32_t)__builtin_clzll(t.lo)) << 8) |
-                                           (uint32_t)__builtin_ctzll(t.hi)
-                                     : 0x20000u + side;
+                token = t.lo && t.hi && (side || meet) ? 0x10000u | ((63u - (uint32_t)__builtin_clzll(t.lo)) << 8) |
+                                                             (uint32_t)__builtin_ctzll(t.hi)
+                                                       : 0x20000u + side;
             a.edge[2 * task + side] = token;
         }
         if (lane >= kLead && lane < 63 && valid) {
