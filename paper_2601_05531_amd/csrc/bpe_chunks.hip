@@ -648,7 +648,9 @@ __global__ __launch_bounds__(64) void k_bpe_walk(ChunkArgs a) {
         int64_t o0 = a.offs[r], o1 = a.offs[r + 1];
         o0 = o0 < 0 ? 0 : (o0 > a.nbytes ? a.nbytes : o0);
         o1 = o1 < o0 ? o0 : (o1 > a.nbytes ? a.nbytes : o1);
-        const int64_t L = o1 - o0, nch = ce - cb;
+        // rows that overlap (malformed offsets) can have more chunks than there
+        // are; the last row then ends with the last chunk
+        const int64_t nch = ce - cb, L = min(o1 - o0, nch * (int64_t)kChunk);
         uint64_t *mask = a.mask + cb, *dead = a.dead + cb;
         uint64_t *old = a.pos + cb;
         const uint8_t *text = a.bytes + o0;
