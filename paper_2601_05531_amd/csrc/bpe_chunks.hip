@@ -43,7 +43,7 @@
 //  3. k_bpe_walk: chunks that did not meet their neighbour within 127 bases
 //     (short tandem repeats), or whose wave ended on other tokens than the
 //     next wave holds: one wave per row carries the search on until it meets
-//     a later chunk's tokens.
+//     a later chunk's tokens, a repeat's tokens at once.
 //  4. k_bpe_count: exclusive scan of the chunks' token counts.
 //  5. k_bpe_put: ids, offsets, specials, pads and mask.
 #include <algorithm>
@@ -67,7 +67,7 @@ constexpr int kMaxTokenBases = 64;     // longer tokens: the item path
 constexpr int kMaxWavesPerGroup = 8;
 constexpr int kMinWavesPerGroup = 2;
 constexpr uint32_t kStepCap = 1u << 20;  // never reached: a lane tries at most 64 tokens at each of 127 bases
-constexpr uint32_t kFailed = 0x80000000u;
+constexpr uint32_t kFailed = 0x80000000u, kTaken = 0x40000000u, kRowBits = 0x3FFFFFFFu;
 constexpr size_t kLdsRoom = 160 * 1024;
 constexpr int kPutNT = 256;
 constexpr int kCountPerThread = 4;
@@ -254,7 +254,8 @@ struct ChunkArgs {
     int64_t max_chunks;
     uint64_t *mask;  // [max_chunks] bit x: a token starts at base x of the chunk
     uint64_t *dead;  // [max_chunks] walk: positions that lead nowhere
-    uint32_t *row;   // [max_chunks] row of the chunk, kFailed: did not meet the next chunk
+    uint32_t *row;   // [max_chunks] row of the chunk, kFailed: did not meet the next chunk; kTaken, on a
+                     // row's first: a workgroup of the walk has the row
     uint32_t *list;  // [max_chunks] chunks with kFailed, in no order
     uint32_t *edge;  // [tasks][2] token across the start and across the end of a wave's own chunks
     uint64_t *pos;   // [max_chunks + 1] tokens before the chunk (walk: the start bits it replaces)
@@ -267,24 +268,10 @@ struct ChunkArgs {
     uint32_t warm;  // bases of the longest token, less one
 };
 
-// Classes of a byte: digit (A0 C1 G2 T3), barrier or base.
-struct ByteClass {
-    uint32_t digit;
-    bool base, n;
-};
-__device__ __forceinline__ ByteClass classify(uint32_t b) {
-    const uint32_t f = b | 0x20u;
-    const uint32_t d = ((f >> 1) ^ (f >> 2)) & 3u;
-    return ByteClass{d, f == ((0x74676361u >> (8 * d)) & 0xFFu), f == 'n'};
-}
-
-struct Planes {
-    uint64_t lo, hi, bar, n;  // per base: low and high digit bit, barrier, N
-};
-__device__ __forceinline__ Planes planes(uint32_t b) {
-    const ByteClass c = classify(b);
-    return Planes{__ballot(c.base && (c.digit & 1u)), __ballot(c.base && (c.digit & 2u)), __ballot(!c.base),
-                  __ballot(c.n)};
+// Digit of a base (A0 C1 G2 T3), 4: N, 5: any other byte.
+__device__ __forceinline__ uint32_t base_class(uint32_t b) {
+    const uint32_t f = b | 0x20u, d = ((f >> 1) ^ (f >> 2)) & 3u;
+    return f == ((0x74676361u >> (8 * d)) & 0xFFu) ? d : f == 'n' ? 4u : 5u;
 }
 
 // 128-bit start mask.
@@ -624,27 +611,38 @@ __global__ __launch_bounds__(64 * kMaxWavesPerGroup) void k_bpe_chunks(ChunkArgs
 
 // Carries the segmentation on, row by row, from each chunk that did not meet
 // its neighbour: the same search with the row's own start bits as its stack,
-// over as many bases as it takes to share a token with the bits that the
-// later chunks left (up to the next chunk that failed), or to the row's end.
-// All lanes of a wave hold the same state and store the same values. Serial,
-// about 0.3 us a base; it serves tandem repeats longer than a lane's 127
-// bases, inside which segmentations from two starting points need not meet.
+// until it shares a token with the bits that the later chunks left (up to the
+// next chunk that failed), or to the row's end. That happens in short tandem
+// repeats, inside which segmentations from two starting points meet only where
+// their distance is a multiple of the bases that the repeated tokens cover, so
+// one may have to go on to the repeat's end. One wave per row: the longest
+// tokens of 64 positions at a time, a token and the next two shorter ones tried
+// together, and, where the tokens taken repeat and the text goes on repeating,
+// the tokens of all repetitions written at once. Bound by the latency of the
+// reads of a step. Whole encodes with the 4,096-merge table, in us, by merge
+// rounds instead of chunks / by a walk of the same stretches that reads one
+// token at a time and knows no cycles / now: CAG repeated to 20,000 bases 985 /
+// 4,180 / 101, to 10^6 12,900 / 208,000 / 1,980; 1,024 rows of 500 to 20,000
+// random bases with a repeat of 40 to 250 every 2,000 1,420 / 2,100 / 765.
+constexpr int kRing = 64;        // tokens remembered, to find a cycle of up to half of them
+constexpr int kCycle = 1024;     // bases of the longest cycle
+constexpr int kCycleEvery = 8;   // tokens between two looks for one
+constexpr int kCycleMin = 96;    // bases that are worth writing at once
 __global__ __launch_bounds__(64) void k_bpe_walk(ChunkArgs a) {
-    const uint32_t entries = *a.count;
+    __shared__ uint16_t s_tok[kRing], s_cycle[kCycle];
+    __shared__ int32_t s_at[kRing];
+    const int64_t entries = *a.count;
     const int lane = threadIdx.x;
     const int64_t total = min(a.chunk_off[a.n], a.max_chunks), tasks = (total + kOwn - 1) / kOwn;
+    const uint32_t longest_token = a.warm + 1;
     // whether chunk c (c < total) does not go on in chunk c + 1
     auto fails = [&](int64_t c) -> bool {
         if (a.row[c] & kFailed) return true;
         const int64_t t = c / kOwn;
         return c == t * kOwn + kOwn - 1 && t + 1 < tasks && a.edge[2 * t + 1] != a.edge[2 * (t + 1)];
     };
-    auto walk = [&](int64_t c0) {
-        const int64_t r = a.row[c0] & ~kFailed;
+    auto walk_row = [&](int64_t r) {
         const int64_t cb = a.chunk_off[r], ce = min(a.chunk_off[r + 1], a.max_chunks);
-        // the wave of the row's first failed chunk takes the whole row
-        for (int64_t k = c0 - 1; k >= cb; k -= 64)
-            if (__ballot(k - lane >= cb && fails(k - lane))) return;
         int64_t o0 = a.offs[r], o1 = a.offs[r + 1];
         o0 = o0 < 0 ? 0 : (o0 > a.nbytes ? a.nbytes : o0);
         o1 = o1 < o0 ? o0 : (o1 > a.nbytes ? a.nbytes : o1);
@@ -655,110 +653,278 @@ __global__ __launch_bounds__(64) void k_bpe_walk(ChunkArgs a) {
         uint64_t *old = a.pos + cb;
         const uint8_t *text = a.bytes + o0;
         uint16_t *sym = a.sym + o0;
+        // Words of start bits and closed positions change by atomic operations
+        // of one lane, which no step waits for, and are read past the L1.
+        auto change = [&](uint64_t *words, int64_t p, bool set) {
+            unsigned long long *w = reinterpret_cast<unsigned long long *>(words + (p >> 6));
+            if (lane == 0) {
+                if (set) atomicOr(w, 1ull << (p & 63));
+                else atomicAnd(w, ~(1ull << (p & 63)));
+            }
+        };
         auto last_start = [&](int64_t p) -> int64_t {  // greatest start below p (p > 0)
             int64_t k = (p - 1) >> 6;
-            uint64_t m = mask[k] & (~0ull >> (63 - ((p - 1) & 63)));
-            while (!m) m = mask[--k];
+            uint64_t m = dev::ld_relaxed(mask + k) & (~0ull >> (63 - ((p - 1) & 63)));
+            while (!m) m = dev::ld_relaxed(mask + --k);
             return (k << 6) + 63 - __builtin_clzll(m);
         };
-        int64_t f = c0 - cb;
+        // the first chunk from k on that fails
+        auto next_failed = [&](int64_t k) -> int64_t {
+            for (; k < nch; k += 64) {
+                const uint64_t hit = __ballot(k + lane < nch && fails(cb + k + lane));
+                if (hit) return k + __builtin_ctzll(hit);
+            }
+            return nch;
+        };
+        // longest token at each of 64 positions, one per lane, and its entry
+        int64_t window = -64;
+        uint32_t best = 0;
+        uint2 best_info{0, 0};
+        auto look = [&](int64_t p) {
+            if (p >= window && p < window + 64) return;
+            window = p;
+            best = 0;
+            if (p + lane < L) {
+                const uint32_t c0 = base_class(text[p + lane]);
+                if (c0 > 3) {
+                    best = c0 == 4 ? 9u : (uint32_t)DNATOK_ID_UNK;
+                } else {
+                    uint32_t node = 0, c = c0;
+                    for (int64_t x = p + lane; x < L && c < 4;) {
+                        ++x;
+                        const uint32_t ahead = x < L ? base_class(text[x]) : 5u;  // asked for beside the node
+                        const uint32_t h = a.kid[4 * node + c];
+                        best = (h & 0xFFFFu) ? h & 0xFFFFu : best;
+                        node = h >> 16;
+                        c = node ? ahead : 5u;
+                    }
+                }
+            }
+            best_info = a.info[best];
+        };
+        int64_t f = next_failed(0);
         while (f < nch) {
             int64_t p = last_start((f + 1) << 6);
+            const int64_t first = p;
             uint32_t prev = p ? sym[last_start(p)] : 0u;
-            int64_t top = f, low = p >> 6;  // chunks entered; chunks whose dead bits are set up
+            int64_t top = f, low = p >> 6;  // chunks entered; chunks whose closed positions are set up
             for (int64_t k = low; k <= top; ++k) dead[k] = 0;
+            bool any_dead = false;
             auto enter = [&](int64_t to) {
                 for (; top < to; ++top) {
-                    old[top + 1] = mask[top + 1];
-                    mask[top + 1] = 0;
-                    dead[top + 1] = 0;
+                    const uint64_t m = dev::ld_relaxed(mask + top + 1);
+                    if (lane == 0) {
+                        old[top + 1] = m;
+                        mask[top + 1] = 0;
+                        dead[top + 1] = 0;
+                    }
                 }
             };
-            int64_t resume = nch;
+            // tokens taken; how many of the last ones the rings hold; those
+            // taken until the next look for a cycle
+            uint32_t taken = 0, kept = 0, until = kCycleEvery;
+            int64_t resume = nch, held_at = -1;
+            uint64_t held = 0;  // old[held_at]
+            bool fresh = true;  // the longest token at p is tried first, else `cand`
             uint32_t cand = 0;
-            bool fresh = true;
+            uint2 x{0, 0};
             for (;;) {
                 if (fresh) {
-                    // longest token at p
-                    const uint32_t b = p + lane < L ? text[p + lane] : 0u;
-                    const Planes w = planes(b);
-                    const uint32_t dist = w.bar ? (uint32_t)__builtin_ctzll(w.bar) : 64u;
-                    if (dist == 0) {
-                        cand = (__ballot(classify(b).n) & 1u) ? 9u : (uint32_t)DNATOK_ID_UNK;
-                    } else {
-                        cand = 0;
-                        uint32_t node = 0, d = 0;
-                        do {
-                            const uint32_t h =
-                                a.kid[4 * node + (uint32_t)(((w.lo >> d) & 1u) | (((w.hi >> d) & 1u) << 1))];
-                            cand = (h & 0xFFFFu) ? h & 0xFFFFu : cand;
-                            node = h >> 16;
-                        } while (node && ++d < dist);
-                    }
+                    look(p);
+                    const uint32_t at = (uint32_t)(p - window);
+                    cand = dev::wave_read_u32(best, at);
+                    x = uint2{dev::wave_read_u32(best_info.x, at), dev::wave_read_u32(best_info.y, at)};
                     fresh = false;
+                } else if (cand) {
+                    x = a.info[cand];
                 }
                 if (cand == 0) {
+                    // nothing fits at p: give the token before it up
                     if (p == 0) {  // never, every base is a token
                         dev::raise_error(a.count - HDR_BPE_FAILED, DNATOK_DERR_INTERNAL);
                         return;
                     }
-                    dead[p >> 6] |= 1ull << (p & 63);
-                    mask[p >> 6] &= ~(1ull << (p & 63));
+                    change(dead, p, true);
+                    change(mask, p, false);
+                    any_dead = true;
                     p = last_start(p);
-                    for (; low > (p >> 6); --low) dead[low - 1] = 0;
-                    prev = p ? sym[last_start(p)] : 0u;
-                    fresh = true;  // longer tokens too: a chunk's search ended at its own last base
+                    for (; low > (p >> 6); --low)
+                        if (lane == 0) dead[low - 1] = 0;
+                    // its end is closed now, so a shorter one follows; a token
+                    // that a chunk's own search took may have ended at the
+                    // chunk's last base, so longer ones are tried too
+                    fresh = kept == 0;
+                    cand = prev;
+                    if (kept) {
+                        --kept;
+                        --taken;
+                    }
+                    prev = kept ? s_tok[(taken - 1) % kRing] : p ? sym[last_start(p)] : 0u;
                     continue;
                 }
-                const uint2 inf = a.info[cand];
-                const int64_t q = p + info_len(inf);
-                const bool blocked = q > L || (q < L && (q >> 6) <= top && ((dead[q >> 6] >> (q & 63)) & 1ull));
-                if (blocked || !((a.compat[prev * a.rw + (cand >> 5)] >> (cand & 31u)) & 1u)) {
-                    cand = info_link(inf);
+                // it and the next two shorter ones, one per lane
+                const uint32_t mine =
+                    lane == 0 ? cand : lane == 1 ? x.x & 0x3FFFu : lane == 2 ? (x.x >> 14) & 0x3FFFu : 0u;
+                const int64_t to = p + 1 + (lane == 0 ? (x.y >> 14) & 63u : lane == 1 ? (x.y >> 20) & 63u : x.y >> 26);
+                bool fits = false;
+                if (mine && to <= L) {
+                    const uint32_t follow = a.compat[prev * a.rw + (mine >> 5)] >> (mine & 31u);
+                    const bool closed =
+                        any_dead && to < L && (to >> 6) <= top && ((dev::ld_relaxed(dead + (to >> 6)) >> (to & 63)) & 1ull);
+                    fits = (follow & 1u) && !closed;
+                }
+                const uint64_t which = __ballot(fits);
+                if (!which) {
+                    cand = x.y & 0x3FFFu;
                     continue;
                 }
-                sym[p] = (uint16_t)cand;
+                const uint32_t lane_of = (uint32_t)__builtin_ctzll(which);
+                cand = dev::wave_read_u32(mine, lane_of);
+                const int64_t q = p + dev::wave_read_u32((uint32_t)(to - p), lane_of);
+                if (lane == 0) sym[p] = (uint16_t)cand;
                 if (q == L) {
                     enter(nch - 1);
                     break;
                 }
                 enter(q >> 6);
-                mask[q >> 6] |= 1ull << (q & 63);
+                change(mask, q, true);
                 // met: the bits it replaces hold this token too, in chunks that met
                 if ((p >> 6) > f) {
                     const int64_t kp = p >> 6, kq = q >> 6;
-                    uint64_t m = old[kp];
+                    if (held_at != kp) {
+                        held_at = kp;
+                        held = old[kp];
+                    }
+                    uint64_t m = held;
                     bool met = (m >> (p & 63)) & 1u;
                     m &= ~((2ull << (p & 63)) - 1);
                     int64_t k = kp;
                     for (; met && k < kq && !m; m = old[++k]) met = !fails(cb + k);
                     met = met && k == kq && m && __builtin_ctzll(m) == (int)(q & 63);
                     if (met) {
-                        const uint64_t lower = (1ull << (q & 63)) - 1;
-                        mask[kq] = (mask[kq] & lower) | (old[kq] & ~lower);
-                        for (int64_t i = kq + 1; i <= top; ++i) mask[i] = old[i];
+                        const uint64_t lower = (1ull << (q & 63)) - 1, m0 = dev::ld_relaxed(mask + kq);
+                        if (lane == 0) {
+                            mask[kq] = (m0 & lower) | (old[kq] & ~lower);
+                            for (int64_t i = kq + 1; i <= top; ++i) mask[i] = old[i];
+                        }
                         resume = kq;
                         break;
                     }
                 }
+                if (lane == 0) {
+                    s_tok[taken % kRing] = (uint16_t)cand;
+                    s_at[taken % kRing] = (int32_t)(p - first);
+                }
+                ++taken;
+                kept = min(kept + 1, (uint32_t)kRing);
                 prev = cand;
                 p = q;
                 fresh = true;
+                wave_sync();
+                if (--until) continue;
+                until = kCycleEvery;
+                // lane i: whether the last i + 1 tokens are those before them once more
+                const uint32_t j = (uint32_t)lane + 1;
+                bool again = 2 * j <= kept;
+                for (uint32_t i = 1; again && i <= j; ++i)
+                    again = s_tok[(taken - i) % kRing] == s_tok[(taken - i - j) % kRing];
+                const uint64_t cycles = __ballot(again);
+                if (!cycles) continue;
+                const uint32_t tokens = (uint32_t)__builtin_ctzll(cycles) + 1u;
+                const int64_t begin = first + s_at[(taken - tokens) % kRing], bases = p - begin;
+                if (bases > kCycle) continue;
+                // where the text stops repeating: 16 bases per lane
+                int64_t end = p;
+                for (;;) {
+                    const int64_t at = end + 16 * lane;
+                    int same = 0;
+                    if (at + 16 <= L) {
+                        uint64_t u[2], v[2];
+                        __builtin_memcpy(u, text + at, 16);
+                        __builtin_memcpy(v, text + at - bases, 16);
+                        const uint64_t d0 = (u[0] ^ v[0]) & ~0x2020202020202020ull;
+                        const uint64_t d1 = (u[1] ^ v[1]) & ~0x2020202020202020ull;
+                        same = d0 ? __builtin_ctzll(d0) / 8 : d1 ? 8 + __builtin_ctzll(d1) / 8 : 16;
+                    } else {
+                        while (at + same < L && ((text[at + same] ^ text[at + same - bases]) & ~0x20u) == 0) ++same;
+                    }
+                    const uint64_t ends = __ballot(same < 16);
+                    if (ends) {
+                        const uint32_t l = (uint32_t)__builtin_ctzll(ends);
+                        end += 16 * l + dev::wave_read_u32((uint32_t)same, l);
+                        break;
+                    }
+                    end += 16 * 64;
+                }
+                // Every pair of the cycle has been found to fit, so the tokens
+                // of its repetitions are the row's as far as the text repeats;
+                // the last bases are left to the search.
+                const int64_t room = end - 2 * (int64_t)longest_token - p;
+                const int64_t past = p + (room > 0 ? room / bases * bases : 0);
+                if (past - p < kCycleMin) continue;
+                for (int64_t o = lane; o < bases; o += 64) s_cycle[o] = 0;
+                wave_sync();
+                if ((uint32_t)lane < tokens) {
+                    const uint32_t i = (taken - tokens + (uint32_t)lane) % kRing;
+                    s_cycle[first + s_at[i] - begin] = s_tok[i];
+                }
+                wave_sync();
+                for (int64_t k = (p >> 6) + lane; k <= past >> 6; k += 64) {
+                    const int64_t x0 = max(k * 64, p), x1 = min(k * 64 + 63, past);
+                    const uint64_t m = dev::ld_relaxed(mask + k);
+                    uint64_t w = 0;
+                    uint32_t o = (uint32_t)((x0 - p) % bases);
+                    for (int64_t y = x0; y <= x1; ++y) {
+                        const uint16_t token = s_cycle[o];
+                        if (token) {
+                            w |= 1ull << (y & 63);
+                            if (y < past) sym[y] = token;
+                        }
+                        o = o + 1 == (uint32_t)bases ? 0u : o + 1;
+                    }
+                    if (k > top) {
+                        old[k] = m;
+                        dead[k] = 0;
+                    } else {
+                        w |= m;
+                    }
+                    mask[k] = w;
+                }
+                __threadfence();
+                top = max(top, past >> 6);
+                p = past;
+                kept = 0;
             }
-            // the next failed chunk from there on
-            f = nch;
-            for (int64_t k = resume; k < nch && f == nch; k += 64) {
-                const uint64_t hit = __ballot(k + lane < nch && fails(cb + k + lane));
-                if (hit) f = k + __builtin_ctzll(hit);
-            }
+            f = next_failed(resume);
         }
     };
-    for (uint32_t e = blockIdx.x; e < entries; e += gridDim.x) walk(a.list[e]);
-    for (int64_t t0 = 64 * (int64_t)blockIdx.x; t0 + 1 < tasks; t0 += 64 * (int64_t)gridDim.x) {
-        const int64_t t = t0 + lane;
-        const int64_t c = t * kOwn + kOwn - 1;
-        uint64_t hit = __ballot(t + 1 < tasks && !(a.row[min(c, total - 1)] & kFailed) && fails(min(c, total - 1)));
-        for (; hit; hit &= hit - 1) walk((t0 + __builtin_ctzll(hit)) * kOwn + kOwn - 1);
+    // Rows with a chunk that fails. A wave looks at 64 such chunks and takes
+    // one row of theirs at a time, so that others find the rest.
+    const int64_t items = entries + max(tasks - 1, (int64_t)0);
+    const uint32_t turn = blockIdx.x % 64;
+    for (int64_t i0 = 0; i0 < items; i0 += (int64_t)gridDim.x * 64) {
+        const int64_t i = i0 + (int64_t)lane * gridDim.x + blockIdx.x;
+        int64_t c = -1, first = 0;
+        if (i < entries) {
+            c = a.list[i];
+        } else if (i < items) {
+            const int64_t k = (i - entries) * kOwn + kOwn - 1;
+            if (!(a.row[k] & kFailed) && fails(k)) c = k;
+        }
+        uint32_t row = 0;
+        if (c >= 0) {
+            row = a.row[c] & kRowBits;
+            first = a.chunk_off[row];
+        }
+        for (;;) {
+            const uint64_t open = __ballot(c >= 0 && !(dev::ld_relaxed32(a.row + first) & kTaken));
+            if (!open) break;
+            const uint64_t turned = turn ? (open >> turn) | (open << (64 - turn)) : open;
+            const uint32_t pick = ((uint32_t)__builtin_ctzll(turned) + turn) % 64;
+            const uint32_t was = (uint32_t)lane == pick ? atomicOr(a.row + first, kTaken) : 0u;
+            const uint32_t mine = dev::wave_read_u32(row, pick);
+            if (!(dev::wave_read_u32(was, pick) & kTaken)) walk_row(mine);
+        }
     }
 }
 
@@ -860,7 +1026,7 @@ __global__ __launch_bounds__(kPutNT) void k_bpe_put(PutArgs a) {
         const uint32_t from = 16 * (uint32_t)(g & 3);
         uint64_t m = all & (0xFFFFull << from);
         const int64_t before = __popcll(all & ((1ull << from) - 1));
-        const int64_t i = a.row[c] & ~kFailed;
+        const int64_t i = a.row[c] & kRowBits;
         const int64_t cb = a.chunk_off[i];
         int64_t o0 = a.offs[i];
         o0 = o0 < 0 ? 0 : (o0 > a.nbytes ? a.nbytes : o0);
@@ -965,10 +1131,10 @@ int launch_bpe_chunks(const dnatok_vocab *v, const uint8_t *d_bytes, int64_t nby
     *used = false;
     // The item path instead: a token of more than 64 bases (the walk reads 64
     // at a time), a table of more states than the automaton's entries hold, a
-    // batch whose chunk indices pass 31 bits, or scratch that holds the item
+    // batch whose chunk indices pass 30 bits, or scratch that holds the item
     // path's arrays but not these.
     const ChunkScratch cs = chunk_scratch(nbytes, n);
-    if (!bt.chunked || cs.max_chunks >= (int64_t)1 << 31 || cs.total > ws->scratch_bytes) return DNATOK_OK;
+    if (!bt.chunked || cs.max_chunks >= (int64_t)1 << 30 || cs.total > ws->scratch_bytes) return DNATOK_OK;
     bool automaton = false;
     uint32_t tables = 0;
     const int most = chunk_waves(v, &automaton, &tables);
@@ -1021,7 +1187,7 @@ int launch_bpe_chunks(const dnatok_vocab *v, const uint8_t *d_bytes, int64_t nby
     DNATOK_HIP(hipFuncSetAttribute((const void *)chunks, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
     hipLaunchKernelGGL(chunks, dim3((unsigned)groups), dim3(64 * waves), lds, stream, a);
     DNATOK_HIP(hipGetLastError());
-    hipLaunchKernelGGL(k_bpe_walk, dim3((unsigned)std::min<int64_t>(n > 0 ? n : 1, cus)), dim3(64), 0, stream, a);
+    hipLaunchKernelGGL(k_bpe_walk, dim3((unsigned)std::min<int64_t>(n > 0 ? n : 1, 8 * (int64_t)cus)), dim3(64), 0, stream, a);
     DNATOK_HIP(hipGetLastError());
 
     CountArgs ca;

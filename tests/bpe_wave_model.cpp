@@ -47,6 +47,11 @@ struct Table {
         return x;
     }
     uint32_t bases(uint32_t t) const { return t >= 5 && t != kN ? (uint32_t)text[t].size() : 1u; }
+    uint32_t longest_bases() const {
+        size_t n = 1;
+        for (const auto &x : text) n = std::max(n, x.size());
+        return (uint32_t)n;
+    }
     // longest token that the len bases at d begin with
     uint32_t longest(const uint8_t *d, int64_t len) const {
         if (d[0] > 3) return d[0] == 4 ? kN : kUnk;
@@ -226,8 +231,10 @@ struct Model {
     }
 
     // Row r's chunks cb.. from the first that does not go on: the search with
-    // the row's own starts as its stack.
-    void walk(int64_t cb, int64_t ce, int64_t *walked) {
+    // the row's own starts as its stack. Where the tokens taken repeat (looked
+    // for every eight, among the last 64), those of all repetitions that the
+    // text goes on with are taken at once.
+    void walk(int64_t cb, int64_t ce, int64_t *walked, int64_t *at_once) {
         const int32_t r = chunks[cb].row;
         const std::vector<uint8_t> &d = rows[r];
         const int64_t L = (int64_t)d.size();
@@ -257,8 +264,11 @@ struct Model {
             std::fill(dead.begin(), dead.end(), 0);
             uint32_t prev = p ? token_at(before(p), p) : 0, cand = t.longest(d.data() + p, L - p);
             int64_t resume = -1;
+            std::vector<std::pair<int64_t, uint32_t>> taken;  // since the last that the search did not take
+            int until = 8;
             for (;;) {
                 if (!cand) {
+                    if (!taken.empty()) taken.pop_back();
                     dead[p] = 1;
                     start[p] = 0;
                     p = before(p);
@@ -285,8 +295,30 @@ struct Model {
                         break;
                     }
                 }
+                taken.push_back({p, cand});
                 prev = cand;
                 p = q;
+                if (--until == 0) {
+                    until = 8;
+                    const size_t n = taken.size();
+                    for (size_t j = 1; 2 * j <= std::min<size_t>(n, 64); ++j) {
+                        bool again = true;
+                        for (size_t i = 1; again && i <= j; ++i) again = taken[n - i].second == taken[n - i - j].second;
+                        if (!again) continue;
+                        const int64_t bases = p - taken[n - j].first;
+                        int64_t end = p;
+                        while (end < L && d[end] == d[end - bases]) ++end;
+                        const int64_t room = std::max<int64_t>(0, end - 2 * (int64_t)t.longest_bases() - p);
+                        const int64_t past = p + room / bases * bases;
+                        if (past - p >= 96) {
+                            for (int64_t x = p + 1; x <= past; ++x) start[x] = start[x - bases];
+                            *at_once += past - p;
+                            p = past;
+                            taken.clear();
+                        }
+                        break;
+                    }
+                }
                 cand = t.longest(d.data() + p, L - p);
             }
             *walked += resume - from;
@@ -321,12 +353,12 @@ struct Model {
         const int64_t tasks = ((int64_t)chunks.size() + own() - 1) / own();
         edge.assign(2 * tasks, 0);
         for (int64_t k = 0; k < tasks; ++k) wave(k, edge_rule);
-        std::fill(stats, stats + 2, 0);  // chunks that did not go on, bases walked
+        std::fill(stats, stats + 3, 0);  // chunks that did not go on, bases walked, of them at once
         for (int64_t c = 0; c < (int64_t)chunks.size(); ++c) stats[0] += fails(c);
         int64_t out = 0;
         for (int32_t r = 0; r < n; ++r) {
             out_offs[r] = out;
-            walk(first[r], first[r + 1], &stats[1]);
+            walk(first[r], first[r + 1], &stats[1], &stats[2]);
             const int64_t L = (int64_t)rows[r].size();
             std::vector<int64_t> at;
             for (int64_t c = first[r]; c < first[r + 1]; ++c)

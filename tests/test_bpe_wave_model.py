@@ -50,7 +50,7 @@ class Model:
     def __call__(self, rows, lanes=64, edge_rule=True):
         data, offs = np.concatenate(rows), synth.offsets_from_lengths([len(r) for r in rows])
         ids, out = np.empty(len(data) + 1, np.int32), np.empty(len(offs), np.int64)
-        stats = np.zeros(2, np.int64)
+        stats = np.zeros(3, np.int64)
         total = self.lib.model_encode(self.h, data.ctypes.data, offs.ctypes.data, len(rows), lanes, int(edge_rule),
                                       ids.ctypes.data, out.ctypes.data, stats.ctypes.data)
         return ids[:total], out, stats
@@ -80,6 +80,12 @@ def test_repeats_over_the_wave_edge(lib):
     tga[3923:3923 + 145] = tandem(b"TGA", 145)
     m.check([tga])
     m.check([poly[:700], tandem(b"TAT", 5000), poly[:0], tandem(b"CAG", 9000)])
+    # repeats out of phase with the chunks inside them are walked to their end
+    for motif in (b"T", b"AC", b"CAG", b"GATA"):
+        rows = [np.concatenate([ACGT[g.integers(0, 4, lead)], tandem(motif, 3000), ACGT[g.integers(0, 4, 50)]])
+                for lead in range(0, 36, 3)]
+        at_once = [m.check([row])[2] for row in rows]
+        assert max(at_once) > 2500 or motif == b"GATA"
     # the case needs the rule: a wave that did not meet its second lane must say so at the edge
     want = oracle.encode(oracle.BPE, tandem(b"TAT", 4300), np.array([0, 4300]), merges=m.merges)[0]
     assert len(m([tandem(b"TAT", 4300)], edge_rule=False)[0]) != len(want)

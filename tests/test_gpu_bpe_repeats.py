@@ -7,7 +7,7 @@ import pytest
 
 import paper_2601_05531_amd as dt
 import synth
-from test_bpe_chunk_rule import ACGT
+from test_bpe_chunk_rule import ACGT, short_token_table
 from test_bpe_wave_model import load, tandem
 from test_gpu_bpe import _packed, _padded
 
@@ -45,6 +45,38 @@ def test_repeats_across_the_wave_edge(table, motif):
         rows.append(row)
     # the same rows behind one another, so the edges fall elsewhere, with empty and short rows between
     _check(*table, [rows[0], rows[1][:0], rows[2], rows[3][:77], rows[4], rows[1]])
+
+
+@pytest.mark.parametrize("motif", [b"T", b"AC", b"CAG", b"AAT", b"GATA", b"TTAGGG"])
+def test_long_repeats_out_of_phase(table, motif):
+    """What precedes a long repeat is out of phase with the chunks inside it
+    for most lengths: its tokens go on to the repeat's end."""
+    g = np.random.default_rng(len(motif))
+    rows = []
+    for n in range(24):
+        tail = ACGT[g.integers(0, 4, int(g.integers(0, 200)))]
+        rows.append(np.concatenate([ACGT[g.integers(0, 4, n)], tandem(motif, int(g.integers(300, 6000))), tail]))
+    rows.append(np.concatenate([rows[5], rows[9], tandem(b"N", 3), rows[11], rows[2]]))
+    soft = np.concatenate([rows[7], tandem(motif, 9000)])
+    soft[::3] |= 0x20
+    rows.append(soft)
+    rows.append(np.concatenate([ACGT[g.integers(0, 4, 77)], tandem(motif, 150000), ACGT[g.integers(0, 4, 77)]]))
+    _check(*table, rows)
+
+
+@pytest.mark.parametrize("seed,R,p_chain,longest", [(1, 6, 0.6, 8), (2, 40, 0.3, 12), (4, 30, 0.6, 32), (5, 60, 0.3, 64)])
+def test_random_tables_long_repeats(seed, R, p_chain, longest):
+    merges = short_token_table(seed, R, p_chain, longest)
+    v = dt.Vocab(dt.BPE, merges=merges)
+    g = np.random.default_rng(seed)
+    rows = []
+    for n in range(60):
+        motif = ACGT[g.integers(0, 4, int(g.integers(1, 40)))].tobytes()
+        lead = ACGT[g.integers(0, 4, int(g.integers(0, 70)))]
+        rows.append(np.concatenate([lead, tandem(motif, int(g.integers(100, 9000))), lead[::-1]]))
+    data, offs = np.concatenate(rows), synth.offsets_from_lengths([len(r) for r in rows])
+    _packed(v, merges, data, offs, cls=False)
+    v.close()
 
 
 def test_small_table_across_the_wave_edge():
