@@ -12,12 +12,13 @@
 // row of D values per token (256 bytes for D = 128 in bf16, against about one
 // input byte). Work is therefore cut by output cells rather than input tiles:
 //  * A block takes a tile of about 32 KiB of output (4 to 1,024 consecutive
-//    cells; cells = tokens plus pads), a thread CPT consecutive cells, so its
-//    ids go out as one 16-byte store and its mask bytes as one word. Every
-//    XCD takes one contiguous part of the tiles. A thread
-//    finds the row of its first cell (PADDED: cell / W with a 32-bit
-//    reciprocal; PACKED: its wave's first and last rows by 64-way searches
-//    over the row starts the row scan wrote, then a binary search between
+//    cells; cells = tokens plus pads), a thread CPT consecutive cells: one, or
+//    four of small rows, whose ids go out as one 16-byte store and their mask
+//    bytes as one word. Every XCD takes one contiguous part of the tiles. A
+//    thread finds the row of its first cell (PADDED: cell / W with a 32-bit
+//    reciprocal; PACKED: its wave looks its first cell's row up, first among
+//    those around the place it would have were all rows equally long, reads that
+//    row and the 63 after it, one per lane, and a thread finds its own among
 //    them) and steps to the next row only at a row end. It places
 //    every cell first (pad, CLS, SEP or body token, and the bytes a body
 //    token reads), then issues all of its reads at once: a k-mer reads the
@@ -34,8 +35,9 @@
 //    is 1 MiB, resident there); the output is the only HBM stream.
 // The store pattern bounds it: the same stores without the lookup take 101 of
 // 103 us when 256 KiB belong to a block in grid order. 4,096 rows of 512
-// bases, 256-byte table rows (541 MB): 103 -> 86 us, a fill of it 78; 300 rows
-// of 3,000 bases as 6-mers: 18.7 -> 13.9; 16 of 1,000: 15.3 -> 6.8.
+// bases, 256-byte table rows (541 MB): 103 -> 79 us, a fill of it 78; 300 rows
+// of 3,000 bases as 6-mers: 18.7 -> 10.5; 1,000 of 50 to 100: 19.4 -> 6.0;
+// PACKED, 100,000 of 20 to 150: 105 -> 89.
 // Bounds: every output index is below the capacity the caller gave; bad
 // offsets are clamped exactly as the row scan clamps them, so cell positions
 // and the written offsets agree.
@@ -50,10 +52,9 @@ namespace {
 constexpr int NT = 256;
 static_assert(NT == kScanNT, "the fused row scan runs with the cell kernel's block size");
 constexpr int64_t kMaxGrid = 1 << 20;        // workgroups of cells
-constexpr int CPT = 4;                       // cells per thread (a multiple of 4)
-constexpr int kMaxCells = NT * CPT;          // cells of a tile
+constexpr int kWalkersPerCu = 20;            // of them, where they take tiles in turn
+constexpr int kMaxCells = NT * 4;            // cells of a tile
 constexpr int kTileBytes = 32768;            // output of a tile, where kMaxCells allows
-constexpr int kCopyUnroll = 8;               // table units loaded before they are stored
 
 enum CwMode { CW_EMBED = 1, CW_GATHER = 2 };
 
@@ -90,6 +91,7 @@ struct CwArgs {
     uint32_t step_cell, step_part;  // NT units in rows and units
     uint32_t *err_hdr;
     int32_t cells;           // cells of a tile, a multiple of CPT
+    int32_t parts;           // every XCD takes one contiguous part of the tiles
     int32_t scan_units;      // PADDED, up to kIndependentMaxRows rows: the first workgroups scan the rows
 };
 
@@ -153,9 +155,8 @@ struct RowFacts {
     int64_t o0, o1, nb, len;
 };
 
-__device__ __forceinline__ RowFacts row_facts(const CwArgs &a, int64_t r) {
+__device__ __forceinline__ RowFacts row_facts(const CwArgs &a, int64_t o0, int64_t o1) {
     RowFacts f;
-    int64_t o0 = a.offs[r], o1 = a.offs[r + 1];
     o0 = o0 < 0 ? 0 : (o0 > a.nbytes ? a.nbytes : o0);
     o1 = o1 < o0 ? o0 : (o1 > a.nbytes ? a.nbytes : o1);
     const int64_t L = o1 - o0;
@@ -168,6 +169,9 @@ __device__ __forceinline__ RowFacts row_facts(const CwArgs &a, int64_t r) {
     f.nb = nb;
     f.len = nb + 2 * a.cls;
     return f;
+}
+__device__ __forceinline__ RowFacts row_facts(const CwArgs &a, int64_t r) {
+    return row_facts(a, a.offs[r], a.offs[r + 1]);
 }
 
 // The 16 bytes from p on, for a k-mer at p (k <= 8 needs three dwords,
@@ -233,18 +237,10 @@ __device__ __forceinline__ int64_t packed_row(const CwArgs &a, int64_t lo, int64
 // at the offsets array, which always holds a readable word), then all
 // reads are issued, then the ids are formed. Rows change within a thread's
 // cells only at row ends.
-template <bool K8>
+template <bool K8, int CPT, bool PADDED>
 __device__ __forceinline__ void thread_cells(const CwArgs &a, const int32_t *s_lut, int64_t cb, int64_t cend,
-                                             int64_t r0, int64_t r1, int32_t (&id)[CPT], bool (&tok)[CPT]) {
-    int64_t row, p;
-    if (a.padded) {
-        row = div_any(cb, a.W, a.winv);
-        p = cb - row * a.W;
-    } else {
-        row = packed_row(a, r0, r1, cb);
-        p = cb - (a.out_offs[row] - a.base);
-    }
-    RowFacts f = row_facts(a, row);
+                                             int64_t row, int64_t p, RowFacts f, int32_t (&id)[CPT],
+                                             bool (&tok)[CPT]) {
     // Fast path: the CPT cells are body tokens of this row whose windows
     // lie within 32 bytes (any overlapping k, frames of k <= 8, table
     // kinds): one 32-byte read, two classifications, then shifts per cell.
@@ -253,10 +249,10 @@ __device__ __forceinline__ void thread_cells(const CwArgs &a, const int32_t *s_l
         const int32_t st = a.lut_kind ? 1 : a.stride;
         const int32_t spanb = (CPT - 1) * st + kw;
         int64_t q0 = p;
-        if (a.padded && a.left) q0 = p - (a.W - f.len);
+        if (PADDED && a.left) q0 = p - (a.W - f.len);
         const int64_t j0 = q0 - a.cls;
         const int64_t s0 = j0 * st;
-        if (spanb <= 32 && cb + CPT <= cend && p + CPT <= (a.padded ? a.W : f.len) && q0 >= a.cls &&
+        if (spanb <= 32 && cb + CPT <= cend && p + CPT <= (PADDED ? a.W : f.len) && q0 >= a.cls &&
             q0 + CPT <= f.len - a.cls && s0 + spanb <= f.o1 - f.o0) {
             const int64_t lo = a.revcomp ? f.o1 - s0 - spanb : f.o0 + s0;
             const uint8_t *pl = a.bytes + lo;
@@ -322,17 +318,17 @@ __device__ __forceinline__ void thread_cells(const CwArgs &a, const int32_t *s_l
         kk[i] = 1;
         tok[i] = false;
         if (cb + i < cend) {
-            if (p == (a.padded ? a.W : f.len)) {
+            if (p == (PADDED ? a.W : f.len)) {
                 // the next row (PACKED: the next non-empty one; one exists,
                 // since this cell is below the total)
                 p = 0;
                 do {
                     ++row;
                     f = row_facts(a, row);
-                } while (!a.padded && f.len == 0);
+                } while (!PADDED && f.len == 0);
             }
             int64_t q = p;
-            if (a.padded && a.left) q = p - (a.W - f.len);
+            if (PADDED && a.left) q = p - (a.W - f.len);
             tok[i] = q >= 0 && q < f.len;
             if (tok[i]) {
                 if (a.cls && q == 0) {
@@ -374,10 +370,11 @@ __device__ __forceinline__ void thread_cells(const CwArgs &a, const int32_t *s_l
     }
 }
 
-template <int MODE, int UB, bool K8>
-__global__ __launch_bounds__(NT) void k_cellwise(CwArgs a) {
+template <int MODE, int UB, bool K8, int CPT, bool PADDED>
+__global__ __launch_bounds__(NT, CPT == 1 && PADDED ? 1 : 5) void k_cellwise(CwArgs a) {
+    constexpr int kCopyUnroll = CPT == 1 ? 8 : 4;  // table units loaded before they are stored
     __shared__ int32_t s_lut[256];
-    __shared__ int64_t s_row[kMaxCells];  // table row of a cell, in bytes; -1: none
+    __shared__ int64_t s_row[NT * CPT];  // table row of a cell, in bytes; -1: none
     const int tid = threadIdx.x;
     const int w = __builtin_amdgcn_readfirstlane(tid / dev::kWave);
     if (MODE != CW_GATHER && (int)blockIdx.x < a.scan_units) {
@@ -387,30 +384,66 @@ __global__ __launch_bounds__(NT) void k_cellwise(CwArgs a) {
         return;
     }
     const int64_t bid = (int64_t)blockIdx.x - a.scan_units;
-    const int64_t G = (int64_t)gridDim.x - a.scan_units;
-    if (MODE != CW_GATHER) s_lut[tid] = a.lut[a.revcomp ? complement((uint32_t)tid) : (uint32_t)tid];
     int64_t total = a.ncells;
     if (total < 0) total = a.out_offs[a.n] - a.base;
     const int64_t limit = total < a.cap ? total : a.cap;
     if (bid == 0 && tid == 0 && total > a.cap) dev::raise_error(a.err_hdr, DNATOK_DERR_CAPACITY);
+    // The tiles there are go to the first blocks, every XCD one part of them
+    // (one tile per block up to kMaxGrid blocks): a grid sized by a buffer of
+    // several times the rows would put them all on the first XCDs.
+    const int64_t G = min((int64_t)gridDim.x - a.scan_units, (limit + a.cells - 1) / a.cells);
+    if (bid >= G) return;
+    if (MODE != CW_GATHER) s_lut[tid] = a.lut[a.revcomp ? complement((uint32_t)tid) : (uint32_t)tid];
     uint32_t err = 0;
     __syncthreads();
 
-    // (one tile per block up to kMaxGrid blocks)
-    for (int64_t c0 = dev::xcd_tile(bid, G) * a.cells; c0 < limit; c0 += G * a.cells) {
+    for (int64_t c0 = (a.parts ? dev::xcd_tile(bid, G) : bid) * a.cells; c0 < limit; c0 += G * a.cells) {
         const int64_t cend = limit - c0 < a.cells ? limit : c0 + a.cells;
-        int64_t r0 = 0, r1 = 0;  // PACKED: rows of the tile's first and last cell
-        const int64_t wb = c0 + w * dev::kWave * CPT;  // the wave's cells
-        if (MODE != CW_GATHER && !a.padded && wb < cend) {
-            const int64_t we = min(wb + dev::kWave * CPT, cend) - 1;
+        const int64_t wb = c0 + w * dev::kWave * CPT;  // the wave's first cell
+        const int64_t cb = c0 + tid * CPT;             // this thread's CPT consecutive cells
+        int64_t row = 0, p = 0;                        // the row of its first one, and the place there
+        RowFacts f{0, 0, 0, 0};
+        if (MODE != CW_GATHER && PADDED && cb < cend) {
+            row = div_any(cb, a.W, a.winv);
+            p = cb - row * a.W;
+            f = row_facts(a, row);
+        }
+        if (MODE != CW_GATHER && !PADDED && wb < cend) {
+            const int64_t n = a.n, we = min(wb + dev::kWave * CPT, cend) - 1;
+            const int lane = tid & (dev::kWave - 1);
             auto past = [&](int64_t key) {
                 return [&a, key](int64_t q) { return a.out_offs[q + 1] - a.base > key; };
             };
-            r0 = dev::wave_lower_bound(0, a.n, past(wb));
-            r1 = past(we)(r0) ? r0 : dev::wave_lower_bound(r0, a.n, past(we));
+            // the row of the wave's first cell, looked for first among the
+            // 4,096 around the one it would be in if all were equally long
+            int64_t lo = 0, hi = n;
+            if (n > 4096) {
+                const int64_t g = min(max((int64_t)((double)wb / (double)total * (double)n) - 2048, (int64_t)0), n - 4096);
+                const uint64_t b = __ballot(past(wb)(g + 64 * (int64_t)lane + 63));
+                const int first = b ? __builtin_ctzll(b) : 64;
+                if (first == 0) hi = g + 63;
+                else if (first == 64) lo = g + 4096;
+                else lo = g + 64 * first, hi = lo + 63;
+            }
+            const int64_t r0 = dev::wave_lower_bound(lo, hi, past(wb));
+            // it and the 63 after it, one per lane
+            const int64_t r = min(r0 + lane, n), r2 = min(r + 1, n);
+            const int64_t start = a.out_offs[r] - a.base, end = a.out_offs[r2] - a.base, o0 = a.offs[r], o1 = a.offs[r2];
+            if (__ballot(end > we)) {
+                int at = 0;  // rows that end at the thread's cell or before
+#pragma unroll
+                for (int d = 32; d > 0; d >>= 1)
+                    if (__shfl((long long)end, at + d - 1, dev::kWave) <= cb) at += d;
+                row = r0 + at;
+                p = cb - __shfl((long long)start, at, dev::kWave);
+                const int64_t x0 = __shfl((long long)o0, at, dev::kWave), x1 = __shfl((long long)o1, at, dev::kWave);
+                f = row_facts(a, x0, x1);
+            } else if (cb < cend) {  // more rows than lanes
+                row = packed_row(a, r0, n, cb);
+                p = cb - (a.out_offs[row] - a.base);
+                f = row_facts(a, row);
+            }
         }
-        // this thread's CPT consecutive cells
-        const int64_t cb = c0 + tid * CPT;
         int32_t id[CPT];
         bool tok[CPT];
 #pragma unroll
@@ -431,14 +464,14 @@ __global__ __launch_bounds__(NT) void k_cellwise(CwArgs a) {
                 }
             }
         } else if (cb < cend) {
-            thread_cells<K8>(a, s_lut, cb, cend, r0, r1, id, tok);
+            thread_cells<K8, CPT, PADDED>(a, s_lut, cb, cend, row, p, f, id, tok);
         }
         if (MODE != CW_GATHER && cb < cend) {
-            const bool full = cb + CPT <= cend;
+            const bool full = CPT % 4 == 0 && cb + CPT <= cend;
             if (a.ids) {
                 if (full && ((reinterpret_cast<uintptr_t>(a.ids + cb) & 15) == 0)) {
 #pragma unroll
-                    for (int g = 0; g < CPT; g += 4)
+                    for (int g = 0; g + 3 < CPT; g += 4)
                         *reinterpret_cast<int4 *>(a.ids + cb + g) = make_int4(id[g], id[g + 1], id[g + 2], id[g + 3]);
                 } else {
 #pragma unroll
@@ -449,7 +482,7 @@ __global__ __launch_bounds__(NT) void k_cellwise(CwArgs a) {
             if (a.mask) {
                 if (full && ((reinterpret_cast<uintptr_t>(a.mask + cb) & 3) == 0)) {
 #pragma unroll
-                    for (int g = 0; g < CPT; g += 4)
+                    for (int g = 0; g + 3 < CPT; g += 4)
                         *reinterpret_cast<uint32_t *>(a.mask + cb + g) = (uint32_t)tok[g] | (uint32_t)tok[g + 1] << 8 |
                                                                          (uint32_t)tok[g + 2] << 16 |
                                                                          (uint32_t)tok[g + 3] << 24;
@@ -494,8 +527,19 @@ __global__ __launch_bounds__(NT) void k_cellwise(CwArgs a) {
 
 template <int MODE, int UB, bool K8>
 int launch_cw(const CwArgs &a, int64_t max_cells, hipStream_t stream) {
-    const int64_t g = std::min(std::max<int64_t>(1, (max_cells + a.cells - 1) / a.cells), kMaxGrid) + a.scan_units;
-    hipLaunchKernelGGL((k_cellwise<MODE, UB, K8>), dim3((unsigned)g), dim3(NT), 0, stream, a);
+    const int64_t most = a.parts ? kMaxGrid : (int64_t)kWalkersPerCu * device_cu_count();
+    const int64_t g = std::min(std::max<int64_t>(1, (max_cells + a.cells - 1) / a.cells), most) + a.scan_units;
+    constexpr bool GATHER = MODE == CW_GATHER;
+    auto *one = a.padded || GATHER ? k_cellwise<MODE, UB, K8, 1, true> : k_cellwise<MODE, UB, K8, 1, GATHER>;
+    auto *four = a.padded || GATHER ? k_cellwise<MODE, UB, K8, 4, true> : k_cellwise<MODE, UB, K8, 4, GATHER>;
+    // PADDED: four workgroups a CU (held by the LDS they ask for), three where
+    // ids come from a byte table and every CU has 16 tiles: the fewer of them
+    // store, the nearer they come to a fill (4,096 rows of 512 bases, 256-byte
+    // table rows: five 87.7 us, four 86.0, three 79.1; 6-mers take longer to
+    // place, 70,000 rows of 50 bases 48.9, 47.2 and 52.4)
+    size_t lds = 0;
+    if (a.padded && a.cells <= NT) lds = a.lut_kind && g > 16 * (int64_t)device_cu_count() ? 46 * 1024 : 34 * 1024;
+    hipLaunchKernelGGL(a.cells <= NT ? one : four, dim3((unsigned)g), dim3(NT), lds, stream, a);
     DNATOK_HIP(hipGetLastError());
     return DNATOK_OK;
 }
@@ -503,8 +547,8 @@ int launch_cw(const CwArgs &a, int64_t max_cells, hipStream_t stream) {
 // k-mers of up to 8 bases read three dwords per token, longer ones five.
 template <int MODE, int UB>
 int launch_cw_k(const CwArgs &a, int64_t max_cells, hipStream_t stream) {
-    if (a.lut_kind || a.k <= 8) return launch_cw<MODE, UB, true>(a, max_cells, stream);
-    return launch_cw<MODE, UB, false>(a, max_cells, stream);
+    if (MODE == CW_GATHER || a.lut_kind || a.k <= 8) return launch_cw<MODE, UB, true>(a, max_cells, stream);
+    return launch_cw<MODE, UB, MODE == CW_GATHER>(a, max_cells, stream);
 }
 
 template <int MODE>
@@ -518,7 +562,13 @@ int launch_cw_units(CwArgs &a, int64_t max_cells, hipStream_t stream) {
     a.ruinv = 0xFFFFFFFFu / a.ru;
     a.step_cell = NT / a.ru;
     a.step_part = NT % a.ru;
-    a.cells = (int32_t)std::min<int64_t>(kMaxCells, std::max<int64_t>(CPT, kTileBytes / a.row_bytes / CPT * CPT));
+    // 32 KiB a tile, one cell per thread: with four, 32 of 256 threads placed a
+    // tile of 256-byte rows (3.5M 6-mers of 100,000 reads 141 us PACKED, this
+    // way 89). Rows of less than 128 bytes: 1,024 cells, four per thread, and up
+    // to 16 KiB a tile in the grid's order, as placing outweighs the stores (41M
+    // cells of 16 bytes PACKED 195 us, in parts 207).
+    a.cells = a.row_bytes < kTileBytes / NT ? kMaxCells : (int32_t)std::max<int64_t>(4, kTileBytes / a.row_bytes / 4 * 4);
+    a.parts = a.cells * a.row_bytes > kTileBytes / 2;
     switch (ub) {
     case 16: return launch_cw_k<MODE, 16>(a, max_cells, stream);
     case 8: return launch_cw_k<MODE, 8>(a, max_cells, stream);
@@ -580,7 +630,9 @@ int setup_encode(CwArgs &a, const dnatok_vocab *v, const uint8_t *d_bytes, int64
     }
     a.err_hdr = ws->d_hdr;
     a.ncells = a.padded ? (int64_t)n * a.W : -1;
-    *max_cells = a.padded ? a.ncells : -1;
+    // PACKED: the most that rows of nbytes together can have
+    const int64_t stride = kmer ? a.stride : 1;
+    *max_cells = a.padded ? a.ncells : nbytes / stride + (stride > 1 || a.overlap ? n : 0) + 2 * (int64_t)a.cls * n;
     return DNATOK_OK;
 }
 
@@ -601,7 +653,7 @@ int launch_embed(const dnatok_vocab *v, const uint8_t *d_bytes, int64_t nbytes, 
     a.n_rows = n_rows;
     a.row_bytes = row_bytes;
     a.emb = static_cast<uint8_t *>(d_out);
-    if (max_cells < 0 || max_cells > out_rows) max_cells = out_rows;
+    if (max_cells > out_rows) max_cells = out_rows;
     return launch_cw_units<CW_EMBED>(a, max_cells, stream);
 }
 
