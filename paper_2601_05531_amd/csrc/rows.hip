@@ -234,8 +234,9 @@ __device__ __forceinline__ void write_pads(const RowsArgs &a, int unit, int lane
 }
 
 // What a launch writes: one vocabulary forward in frames; one vocabulary
-// reverse complemented or in overlapping windows; several vocabularies.
-enum RowsMode { ROWS_PLAIN = 0, ROWS_VARIANT = 1, ROWS_MULTI = 2 };
+// reverse complemented or in overlapping windows; several vocabularies; as the
+// second, a tile's waves all staging it and writing a quarter of its groups each.
+enum RowsMode { ROWS_PLAIN = 0, ROWS_VARIANT = 1, ROWS_MULTI = 2, ROWS_SHARED = 3 };
 
 // ROWS_MULTI: a tile of four times the bytes belongs to the workgroup, whose
 // waves stage a quarter each and, after one barrier, write one vocabulary
@@ -264,8 +265,9 @@ __global__ __launch_bounds__(NTR) void k_rows(RowsArgs a) {
     constexpr bool MULTI = MODE == ROWS_MULTI, PLAIN = MODE == ROWS_PLAIN;
     const bool extra = (int)blockIdx.x < a.lead;
     int64_t tile = extra ? (PADDED ? b - a.pads : b) : (int64_t)blockIdx.x - a.lead;
-    if (!MULTI) tile = tile * kRowWaves + wave;
-    const bool rc = MODE == ROWS_VARIANT && a.revcomp != 0, overlap = MODE == ROWS_VARIANT && a.overlap != 0;
+    constexpr bool shared = MODE == ROWS_SHARED, VARIANT = MODE == ROWS_VARIANT || shared;
+    if (!MULTI && !shared) tile = tile * kRowWaves + wave;
+    const bool rc = VARIANT && a.revcomp != 0, overlap = VARIANT && a.overlap != 0;
     constexpr int64_t T = 1024 * U * (MULTI ? kRowWaves : 1);
     constexpr uint32_t nch = (uint32_t)(T / 16);
     uint8_t *lds = MULTI ? dyn : dyn + (size_t)wave * a.wave_lds;
@@ -274,7 +276,8 @@ __global__ __launch_bounds__(NTR) void k_rows(RowsArgs a) {
     const int share = MULTI && a.nv == 2 ? 2 : 1;
     const int v0 = MULTI ? wave / share : 0, vstep = MULTI ? kRowWaves / share : 1;
     const int32_t nv = MULTI ? a.nv : 1;
-    const int32_t l0 = lane + (MULTI ? 64 * (wave % share) : 0), lstep = 64 * share;
+    const int32_t l0 = lane + (MULTI ? 64 * (wave % share) : shared ? 64 * wave : 0);
+    const int32_t lstep = shared ? 64 * kRowWaves : 64 * share;
     const uint32_t m0 = MULTI ? (uint32_t)wave * 64u * U : 0u;  // first chunk this wave stages
     uint64_t *win64 = reinterpret_cast<uint64_t *>(lds);
     uint32_t *val32 = reinterpret_cast<uint32_t *>(win64 + nch + 2);
@@ -569,7 +572,7 @@ __global__ __launch_bounds__(NTR) void k_rows(RowsArgs a) {
             const uint32_t nrows = (uint32_t)__popcll(with);
             const uint32_t all = dev::wave_read_u32(dev::wave_incl_sum_u32((uint32_t)ngroups), 63);
             run.before = run.nfast = run.pad0 = run.npad = 0;
-            if (all >= kLongRun * nrows) {
+            if (all >= (shared ? kRowWaves : 1) * kLongRun * nrows) {
                 // groups of four full frames, and of four pads
                 const int32_t fhi = PADDED ? run.f1 : (int32_t)min((int64_t)run.f1, max(o.cap - run.dlo, (int64_t)0));
                 const int32_t cA = run.f0 + ((4 - ((m + run.f0) & 3)) & 3);
@@ -695,12 +698,6 @@ __global__ __launch_bounds__(NTR) void k_rows(RowsArgs a) {
 template <bool KMER, int U>
 int launch_one(RowsArgs a, hipStream_t stream) {
     const bool multi = a.nv > 1, plain = !multi && !a.revcomp && !a.overlap;
-    auto *kernel = a.padded ? (plain   ? k_rows<KMER, U, true, ROWS_PLAIN>
-                               : multi ? k_rows<true, U, true, ROWS_MULTI>
-                                       : k_rows<KMER, U, true, ROWS_VARIANT>)
-                            : (plain   ? k_rows<KMER, U, false, ROWS_PLAIN>
-                               : multi ? k_rows<true, U, false, ROWS_MULTI>
-                                       : k_rows<KMER, U, false, ROWS_VARIANT>);
     const int64_t T = 1024 * U * (multi ? kRowWaves : 1);
     a.ntiles = std::max<int64_t>(1, (a.nbytes + a.shift + T - 1) / T);
     const uint32_t stage = stage_bytes<KMER>((uint32_t)(T / 16));
@@ -708,10 +705,26 @@ int launch_one(RowsArgs a, hipStream_t stream) {
     const size_t dyn = (multi ? stage + (size_t)kRowWaves * kRunBytes : (size_t)kRowWaves * a.wave_lds) +
                        (a.self_scan ? 8 * (size_t)kSelfScanRows : 0);
     const int32_t extra = a.n > 0 ? (a.n - 1) / 64 : 0;
+    // A variant's cell takes some 20 instructions more than a plain one, and a
+    // small batch leaves most of the chip idle: 1,000 rows of 50 to 100 bases
+    // PADDED as overlapping 6-mers take 15.1 us with a wave per tile, 7.3 with
+    // four. Past two tiles a CU, or with more 64-row steps than tiles, the
+    // staging done four times costs more (10^6 bases 7.7 and 8.2 us).
+    const bool shared = !multi && !plain && U == 1 && extra <= a.ntiles && a.ntiles <= 2 * (int64_t)device_cu_count();
+    const int per_group = multi || shared ? 1 : kRowWaves;  // tiles
+    constexpr RowsMode SHARED = U == 1 ? ROWS_SHARED : ROWS_VARIANT;
+    auto *kernel = a.padded ? (plain    ? k_rows<KMER, U, true, ROWS_PLAIN>
+                               : multi  ? k_rows<true, U, true, ROWS_MULTI>
+                               : shared ? k_rows<KMER, U, true, SHARED>
+                                        : k_rows<KMER, U, true, ROWS_VARIANT>)
+                            : (plain    ? k_rows<KMER, U, false, ROWS_PLAIN>
+                               : multi  ? k_rows<true, U, false, ROWS_MULTI>
+                               : shared ? k_rows<KMER, U, false, SHARED>
+                                        : k_rows<KMER, U, false, ROWS_VARIANT>);
     a.pads = (a.pad_units + kRowWaves - 1) / kRowWaves;
-    a.lead = a.nv * a.scan_units + a.pads + (multi ? extra : (extra + kRowWaves - 1) / kRowWaves);
+    a.lead = a.nv * a.scan_units + a.pads + (extra + per_group - 1) / per_group;
     a.lead = (a.lead + 7) / 8 * 8;  // keeps tile workgroup b on XCD b % 8
-    const int64_t grid = a.lead + (multi ? a.ntiles : (a.ntiles + kRowWaves - 1) / kRowWaves);
+    const int64_t grid = a.lead + (a.ntiles + per_group - 1) / per_group;
     if (dyn > 64 * 1024)
         DNATOK_HIP(hipFuncSetAttribute((const void *)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)dyn));
     hipLaunchKernelGGL(kernel, dim3((unsigned)grid), dim3(NTR), dyn, stream, a);
