@@ -92,7 +92,7 @@ struct CwArgs {
     uint32_t *err_hdr;
     int32_t cells;           // cells of a tile, a multiple of CPT
     int32_t parts;           // every XCD takes one contiguous part of the tiles
-    int32_t scan_units;      // PADDED, up to kIndependentMaxRows rows: the first workgroups scan the rows
+    int32_t scan_units;      // PADDED, up to kFusedScanRows rows: the first workgroups scan the rows
 };
 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
@@ -610,7 +610,7 @@ int setup_encode(CwArgs &a, const dnatok_vocab *v, const uint8_t *d_bytes, int64
     Workspace *ws = nullptr;
     int rc = get_workspace(stream, 1, &ws);
     if (rc) return rc;
-    a.scan_units = a.padded && n <= kIndependentMaxRows ? (int32_t)rowscan_units(n) : 0;
+    a.scan_units = a.padded && n <= kFusedScanRows ? (int32_t)rowscan_units(n) : 0;
     a.scan_out = d_out_offsets;
     if (!a.scan_units) {
         RowScanSpec sp;

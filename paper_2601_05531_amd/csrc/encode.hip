@@ -2,7 +2,7 @@
 // tile size of an encode, and its dispatch to the wave-tile kernel.
 //
 // Every row's token count has a closed form (L, ceil(L/k) or L - k + 1, plus
-// 2 with CLS/SEP), so out_offsets is a scan over rows: up to 65,536 rows by
+// 2 with CLS/SEP), so out_offsets is a scan over rows: up to 12,288 rows by
 // workgroups that do not wait for each other (k_rowscan_units), longer
 // batches in units of 4,096 rows handed out by ticket and chained with a
 // decoupled look-back (k_rowscan).

@@ -46,7 +46,6 @@ namespace {
 constexpr int NTR = 256;               // threads: four independent waves
 constexpr int kRowWaves = NTR / 64;
 constexpr int kRowVocabs = 8;
-constexpr int32_t kFuseScanRows = 65536;  // PADDED: the row scan shares the launch
 constexpr int32_t kSelfScanRows = 2 * NTR;  // PACKED, one vocabulary: each workgroup scans the rows itself
 // Pads of a row belong to the tile of its last byte (on the left: first), and
 // one wave writes about 4,400 cells a microsecond. Above this row width, or
@@ -772,7 +771,7 @@ int launch_encode_rows(const dnatok_vocab *const *vs, int nv, const uint8_t *d_b
     a.err_hdr = ws->d_hdr;
     // (the variants' kernel takes the scan from its own launch)
     a.self_scan = !a.padded && nv == 1 && !a.revcomp && !a.overlap && n <= kSelfScanRows ? 1 : 0;
-    const bool fused = a.padded && n <= kFuseScanRows;
+    const bool fused = a.padded && n <= kFusedScanRows;
     a.scan_units = fused ? (int32_t)rowscan_units(n) : 0;
     double cells = 0;
     for (int vi = 0; vi < nv; ++vi) {

@@ -124,11 +124,17 @@ struct RowLen {
 // few thousand rows is bound by the latency of its dependent steps, and this
 // form has three (offsets, block scan, stores): 3,001 rows take 5.4 us,
 // where the chained units with their ticket and look-back took 10.4. The
-// reads grow with the square of the rows (8 MB at 65,536), so longer batches
-// keep the chained form.
+// reads grow with the square of the rows (8 MB at 65,536). In a launch of its
+// own it is the shorter form up to kIndependentMaxRows: PACKED encodes of rows
+// of about 1,000 bases, this way / chained, in us, single-nucleotide and 6-mer
+// ids: 8,192 rows 18.4 / 22.8 and 19.3 / 22.5, 16,384 31.6 / 32.4 and 27.6 /
+// 25.1, 65,536 107 / 84 and 80 / 43. In front of the workgroups of an encode
+// or a lookup, which hide it, up to kFusedScanRows: 16,384 rows as 6-mers
+// PADDED 16.9, by a launch of its own 25.7; 65,536 49.6 and 50.3.
 constexpr int kScanRows = 1024;
 constexpr int kScanRowsPerThread = kScanRows / kScanNT;
-constexpr int32_t kIndependentMaxRows = 65536;
+constexpr int32_t kIndependentMaxRows = 12288;
+constexpr int32_t kFusedScanRows = 65536;
 [[maybe_unused]] __host__ __device__ inline int64_t rowscan_units(int64_t n) {
     return n > 0 ? (n + kScanRows - 1) / kScanRows : 1;
 }
