@@ -201,7 +201,9 @@ int ensure_scratch(Workspace *ws, int64_t bytes) {
     DNATOK_HIP(dev_alloc(&p, (size_t)nb));
     ws->d_scratch = static_cast<uint8_t *>(p);
     ws->scratch_bytes = nb;
-    return DNATOK_OK;
+    // a first decode under capture must find its words, as it would not fit
+    // this scratch at any size
+    return ensure_decode(ws);
 }
 
 // ---- fixed scratch (dnatok_encode_noalloc) ---------------------------------------

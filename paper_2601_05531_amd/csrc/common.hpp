@@ -131,8 +131,9 @@ enum HdrSlot {
     HDR_BPE_FAILED = 20
 };
 
-// Tiles of a decode's scan whose words a workspace holds (134M
-// single-nucleotide ids, 67M k-mers); longer decodes clear words of their own
+// Tiles of a decode's scan whose words a workspace holds (268M
+// single-nucleotide ids, 134M k-mers of up to six bases, 33M of more than
+// twelve); longer decodes clear words of their own
 // in the scratch with a launch before them.
 constexpr int64_t kDecodeTiles = 16384;
 constexpr int64_t kDecodeWords = 16 + 2 * (kDecodeTiles + kDecodeTiles / 64 + kDecodeTiles / 4096);
@@ -143,7 +144,8 @@ struct Workspace {
     uint64_t *d_status = nullptr;  // 2 * cap words (parity 0 then parity 1)
     int64_t cap = 0;               // tiles
     int64_t high_water = 0;        // tiles that may hold non-zero status
-    uint64_t *d_decode = nullptr;  // kDecodeWords words of the decode's scan over tiles, from the first decode on
+    uint64_t *d_decode = nullptr;  // kDecodeWords words of the decode's scan over tiles, from the first decode
+                                   // or the first scratch on
     uint8_t *d_scratch = nullptr;  // general scratch for multi-pass kernels (BPE)
     int64_t scratch_bytes = 0;
     bool fixed = false;            // lives in the library's fixed device array: never grows
