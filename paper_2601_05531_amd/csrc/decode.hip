@@ -261,28 +261,18 @@ __device__ __forceinline__ void put_rows(const DecodeArgs &a, const TileRows &ro
                                          int64_t base, F bytes_at) {
     const int64_t w0 = rows.g0, end = last ? INT64_MAX : P0 + tt;
     auto offset = [&](int64_t i) { return i >= w0 && i - w0 < dev::kWave ? rows.po[i - w0] : a.offs[i]; };
-    auto bytes = [&](int64_t o) { return base + bytes_at((int32_t)min(max(o - P0, (int64_t)0), tt)); };
-    int64_t i = rows.ia + threadIdx.x;
-    int64_t o = i < a.n ? offset(i) : end;
-    if (i >= a.n || o >= end) return;
-    int64_t at = bytes(o);
-    a.out_offs[i] = at;
-    // more rows than threads (empty rows, rows of a few ids): four in flight,
-    // equal places looked up once (100,000 empty rows 152 us one by one, 90
-    // this way)
-#pragma unroll 1
-    for (i += NT; i < a.n; i += 4 * NT) {
-        int64_t x[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) x[u] = i + u * NT < a.n ? offset(i + u * NT) : INT64_MAX;
-#pragma unroll 1
-        for (int u = 0; u < 4; ++u) {
-            const int64_t y = u == 0 ? x[0] : u == 1 ? x[1] : u == 2 ? x[2] : x[3];
-            if (i + u * NT >= a.n || y >= end) return;
-            if (y != o) at = bytes(y);
-            o = y;
-            a.out_offs[i + u * NT] = at;
-        }
+    int64_t i = rows.ia + threadIdx.x, o = i < a.n ? offset(i) : INT64_MAX;
+    // a tile of more rows than threads (empty rows, rows of a few ids): the next
+    // row's place asked for ahead, equal places looked up once (100,000 empty
+    // rows 152 us without, 86 so)
+    int64_t seen = -1, at = 0;
+    while (o < end && i < a.n) {
+        const int64_t next = i + NT < a.n ? offset(i + NT) : INT64_MAX;
+        if (o != seen) at = base + bytes_at((int32_t)min(max(o - P0, (int64_t)0), tt));
+        seen = o;
+        a.out_offs[i] = at;
+        i += NT;
+        o = next;
     }
 }
 
