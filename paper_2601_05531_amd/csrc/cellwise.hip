@@ -564,11 +564,14 @@ int launch_cw_units(CwArgs &a, int64_t max_cells, hipStream_t stream) {
     a.step_part = NT % a.ru;
     // 32 KiB a tile, one cell per thread: with four, 32 of 256 threads placed a
     // tile of 256-byte rows (3.5M 6-mers of 100,000 reads 141 us PACKED, this
-    // way 89). Rows of less than 128 bytes: 1,024 cells, four per thread, and up
-    // to 16 KiB a tile in the grid's order, as placing outweighs the stores (41M
-    // cells of 16 bytes PACKED 195 us, in parts 207).
-    a.cells = a.row_bytes < kTileBytes / NT ? kMaxCells : (int32_t)std::max<int64_t>(4, kTileBytes / a.row_bytes / 4 * 4);
-    a.parts = a.cells * a.row_bytes > kTileBytes / 2;
+    // way 89). Rows of less than 128 bytes, four cells per thread, and where
+    // they are placed 1,024 of them, up to 16 KiB a tile in the grid's order, as
+    // placing outweighs the stores (41M cells of 16 bytes PACKED 195 us, in
+    // parts 207; 5M given ids of 64 bytes 55 us in tiles of 512, of 1,024 62).
+    const int64_t fit = std::max<int64_t>(4, kTileBytes / a.row_bytes / 4 * 4);
+    const bool small = MODE != CW_GATHER && a.row_bytes < kTileBytes / NT;
+    a.cells = small ? kMaxCells : (int32_t)std::min<int64_t>(fit, kMaxCells);
+    a.parts = !small || a.cells * a.row_bytes > kTileBytes / 2;
     switch (ub) {
     case 16: return launch_cw_k<MODE, 16>(a, max_cells, stream);
     case 8: return launch_cw_k<MODE, 8>(a, max_cells, stream);
