@@ -67,6 +67,7 @@ constexpr int kMaxTokenBases = 64;     // longer tokens: the item path
 constexpr int kMaxWavesPerGroup = 8;
 constexpr int kMinWavesPerGroup = 2;
 constexpr uint32_t kStepCap = 1u << 20;  // never reached: a lane tries at most 64 tokens at each of 127 bases
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4), aligned(4)));  // (rows start at any byte)
 constexpr uint32_t kFailed = 0x80000000u, kTaken = 0x40000000u, kRowBits = 0x3FFFFFFFu;
 constexpr size_t kLdsRoom = 160 * 1024;
 constexpr int kPutNT = 256;
@@ -389,11 +390,9 @@ __global__ __launch_bounds__(64 * kMaxWavesPerGroup) void k_bpe_chunks(ChunkArgs
             if (__ballot(end && last < 4 * kGroups + 3) == 0) {
 #pragma unroll
                 for (int i = 0; i <= kGroups; ++i) {
-                    const uint4 v = end ? *reinterpret_cast<const uint4 *>(src + 4 * i) : uint4{0, 0, 0, 0};
-                    w[4 * i] = v.x;
-                    w[4 * i + 1] = v.y;
-                    w[4 * i + 2] = v.z;
-                    w[4 * i + 3] = v.w;
+                    const u32x4 v = end ? *reinterpret_cast<const u32x4 *>(src + 4 * i) : u32x4{0, 0, 0, 0};
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) w[4 * i + q] = v[q];
                 }
             } else {
 #pragma unroll
