@@ -720,9 +720,9 @@ def bpe_leg(reps: int = 10, tuning=None, per_seq_leg: bool = True):
         "tokens": tokens,
         "ranks_per_row": {
             "note": "ranks each row applies (distinct ranks in its tokens' merge trees; every row is one ACGT "
-                    "run, so one item): the rounds of a one-rank-per-round merge. The kernel merges the ranks "
-                    "present in a window above the lowest one in a single round where that is exact, so its "
-                    "rounds are fewer; the fused call's critical path is the row with the most ranks",
+                    "run): a property of the rows, the rounds that merging one rank after another would take. "
+                    "The kernels that serve this table segment 64-base chunks by compatible neighbour tokens "
+                    "and apply no ranks",
             "max": int(rounds.max()), "p50": float(np.median(rounds)), "p90": float(np.percentile(rounds, 90)),
             "mean": float(rounds.mean()),
             "hist_edges": [0, 100, 200, 400, 800, 1200, 1600, 2400],
@@ -735,7 +735,6 @@ def bpe_leg(reps: int = 10, tuning=None, per_seq_leg: bool = True):
         "fused_tokens_per_s": tokens / (fused_ms * 1e-3),
         "fused_bases_per_s": nbytes / (fused_ms * 1e-3),
     }
-    out["us_per_rank_on_critical_path"] = round(fused_ms * 1e3 / max(1, int(rounds.max())), 3)
     if not per_seq_leg:
         log("bpe: fused %.3f ms (%.3e tokens/s)" % (fused_ms, out["fused_tokens_per_s"]))
         return out, data, offs, merges

@@ -174,8 +174,10 @@ int dnatok_encode_plan(const dnatok_vocab *v, const int64_t *h_offsets, int32_t 
 
 /*
  * Encode a ragged batch on the device (bytes path: the LUT, k-mer packing,
- * specials and padding all run in one HIP launch; BPE adds its merge rounds).
- *  d_bytes        device uint8[nbytes], any alignment.
+ * specials and padding run in one or two HIP launches, BPE in five or more).
+ *  d_bytes        device uint8[nbytes], any alignment. The ends are read in
+ *                 whole 16-byte-aligned units: up to 15 bytes before the first
+ *                 and after the last byte are read too and have no effect.
  *  d_offsets      device int64[n + 1]: row i is d_bytes[off[i] .. off[i+1]).
  *                 Must be non-decreasing within [0, nbytes].
  *  d_ids          device int32 output, ids_capacity elements. PACKED: row i

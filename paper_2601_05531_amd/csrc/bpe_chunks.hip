@@ -1,6 +1,13 @@
 // Ranked-merge BPE by compatible neighbours: every lane of the chip segments
 // its own short chunk of a row, and neighbouring chunks are stitched.
 //
+// The rule that two tokens may be neighbours, the test for it by undoing their
+// merges, and the search over such tokens from the longest down are published:
+// van Antwerpen and Neubeck, "So many tokens, so little time: Introducing a
+// faster, more flexible byte-pair tokenizer" (GitHub, 2024), and their
+// open-source bpe crate. The lanes, the stitch, the joins between waves and the
+// walk over repeats are this library's.
+//
 // Why that is exact. Call two tokens compatible when the merges, applied to
 // their concatenated bases, leave exactly those two tokens. A sequence of
 // tokens is the segmentation of its text if and only if every adjacent pair
@@ -38,7 +45,8 @@
 // with everything.
 //
 // Pipeline (all on the caller's stream):
-//  1. k_rowscan (encode.hip): chunk offsets of the rows, 64 bases per chunk.
+//  1. k_rowscan_units or k_rowscan (encode.hip, by the number of rows): chunk
+//     offsets of the rows, 64 bases per chunk.
 //  2. k_bpe_chunks: one lane per chunk; start bits and ids of the tokens.
 //  3. k_bpe_walk: chunks that did not meet their neighbour within 127 bases
 //     (short tandem repeats), or whose wave ended on other tokens than the
@@ -83,7 +91,7 @@ __host__ __device__ inline uint2 info_entry(uint32_t c1, uint32_t c2, uint32_t c
 __host__ __device__ inline uint32_t info_link(uint2 x) { return x.x & 0x3FFFu; }
 __host__ __device__ inline uint32_t info_len(uint2 x) { return ((x.y >> 14) & 63u) + 1u; }
 
-// Whether the spines of tokens (x, y) allow the boundary between them: undo
+// Whether tokens (x, y) may be neighbours (the published test, see above): undo
 // the merges of the two, the later one first (equal ranks: leftmost merged
 // first, so the right one is undone first). While a boundary pair stands, it
 // must not rank before the merge that ended it.
@@ -371,7 +379,6 @@ __global__ __launch_bounds__(64 * kMaxWavesPerGroup) void k_bpe_chunks(ChunkArgs
         const int lead = first < 0 ? (int)-first : 0;
         const int64_t base = (int64_t)__shfl((long long)s, lead, 64);
         const bool in_text = valid && s >= base && s - base <= 63 * kChunk;  // fails for malformed offsets only
-        const uint32_t idx = in_text ? (uint32_t)(s - base) : 0u;
         // the last lane reads its own bases only: what follows is the next wave's
         const uint32_t end = in_text ? (uint32_t)min(left, (int64_t)(lane == 63 ? kChunk : kReach)) : 0u;
 
