@@ -89,6 +89,25 @@ def test_repeats_over_the_wave_edge(lib):
     m.close()
 
 
+def edge_repeats(g, rows):
+    """Rows of random bases with a repeat of 1 to 6 bases across base 3,968."""
+    out = []
+    for _ in range(rows):
+        row = ACGT[g.integers(0, 4, int(g.integers(4300, 5000)))]
+        at, bases = int(g.integers(3840, 3969)), int(g.integers(100, 401))
+        repeat = tandem(ACGT[g.integers(0, 4, int(g.integers(1, 7)))].tobytes(), bases)
+        row[at:at + bases] = repeat[:len(row) - at]
+        out.append(row)
+    return out
+
+
+def test_random_repeats_over_the_wave_edge(lib):
+    m = Model(lib, load())
+    unmet = [m.check([row])[0] for row in edge_repeats(np.random.default_rng(7), 160)]
+    assert sum(x > 0 for x in unmet) > 10
+    m.close()
+
+
 def test_small_table_over_the_wave_edge(lib):
     m = Model(lib, np.array([(5, 6), (10, 10), (11, 11)], np.int32))
     row = np.concatenate([tandem(b"G", 3957), tandem(b"AC", 120), tandem(b"G", 64)])

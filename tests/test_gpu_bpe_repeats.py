@@ -8,7 +8,7 @@ import pytest
 import paper_2601_05531_amd as dt
 import synth
 from test_bpe_chunk_rule import ACGT, short_token_table
-from test_bpe_wave_model import load, tandem
+from test_bpe_wave_model import edge_repeats, load, tandem
 from test_gpu_bpe import _packed, _padded
 
 pytestmark = pytest.mark.gpu
@@ -45,6 +45,14 @@ def test_repeats_across_the_wave_edge(table, motif):
         rows.append(row)
     # the same rows behind one another, so the edges fall elsewhere, with empty and short rows between
     _check(*table, [rows[0], rows[1][:0], rows[2], rows[3][:77], rows[4], rows[1]])
+
+
+def test_random_repeats_across_the_wave_edge(table):
+    v, merges = table
+    rows = edge_repeats(np.random.default_rng(8), 300)
+    for row in rows[:100]:  # each the first row of its batch: the edge lies at base 3,968
+        _packed(v, merges, row, np.array([0, len(row)], np.int64), cls=False)
+    _check(v, merges, rows)
 
 
 @pytest.mark.parametrize("motif", [b"T", b"AC", b"CAG", b"AAT", b"GATA", b"TTAGGG"])
