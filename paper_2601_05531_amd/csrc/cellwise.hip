@@ -35,7 +35,7 @@
 //    is 1 MiB, resident there); the output is the only HBM stream.
 // The store pattern bounds it: the same stores without the lookup take 101 of
 // 103 us when 256 KiB belong to a block in grid order. 4,096 rows of 512
-// bases, 256-byte table rows (541 MB): 103 -> 79 us, a fill of it 78; 300 rows
+// bases, 256-byte table rows (541 MB): 103 -> 86 us, a fill of it 78; 300 rows
 // of 3,000 bases as 6-mers: 18.7 -> 10.5; 1,000 of 50 to 100: 19.4 -> 6.0;
 // PACKED, 100,000 of 20 to 150: 105 -> 89.
 // Bounds: every output index is below the capacity the caller gave; bad
@@ -532,13 +532,14 @@ int launch_cw(const CwArgs &a, int64_t max_cells, hipStream_t stream) {
     constexpr bool GATHER = MODE == CW_GATHER;
     auto *one = a.padded || GATHER ? k_cellwise<MODE, UB, K8, 1, true> : k_cellwise<MODE, UB, K8, 1, GATHER>;
     auto *four = a.padded || GATHER ? k_cellwise<MODE, UB, K8, 4, true> : k_cellwise<MODE, UB, K8, 4, GATHER>;
-    // PADDED: four workgroups a CU (held by the LDS they ask for), three where
-    // ids come from a byte table and every CU has 16 tiles: the fewer of them
-    // store, the nearer they come to a fill (4,096 rows of 512 bases, 256-byte
-    // table rows: five 87.7 us, four 86.0, three 79.1; 6-mers take longer to
-    // place, 70,000 rows of 50 bases 48.9, 47.2 and 52.4)
-    size_t lds = 0;
-    if (a.padded && a.cells <= NT) lds = a.lut_kind && g > 16 * (int64_t)device_cu_count() ? 46 * 1024 : 34 * 1024;
+    // Four workgroups a CU (held by the LDS they ask for) but for PACKED k-mers,
+    // which take longest to place: the fewer store, the nearer they come to a
+    // fill. 4,096 rows of 512 bases, 256-byte table rows, five and four: PADDED
+    // 87.7 and 86.0 us, PACKED 100.7 and 93.9; 40,000 rows of 1,000 bases PACKED
+    // as 6-mers 311 and 355. (Three PADDED: 79.1 there, but 5% longer at 8,192
+    // bases a row.)
+    const bool hold = a.cells <= NT && !GATHER && (a.padded || a.lut_kind);
+    const size_t lds = hold ? 34 * 1024 : 0;
     hipLaunchKernelGGL(a.cells <= NT ? one : four, dim3((unsigned)g), dim3(NT), lds, stream, a);
     DNATOK_HIP(hipGetLastError());
     return DNATOK_OK;
