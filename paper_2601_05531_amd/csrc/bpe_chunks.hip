@@ -627,9 +627,9 @@ __global__ __launch_bounds__(64 * kMaxWavesPerGroup) void k_bpe_chunks(ChunkArgs
 // the tokens of all repetitions written at once. Bound by the latency of the
 // reads of a step. Whole encodes with the 4,096-merge table, in us, by merge
 // rounds instead of chunks / by a walk of the same stretches that reads one
-// token at a time and knows no cycles / now: CAG repeated to 20,000 bases 985 /
-// 4,180 / 101, to 10^6 12,900 / 208,000 / 1,980; 1,024 rows of 500 to 20,000
-// random bases with a repeat of 40 to 250 every 2,000 1,420 / 2,100 / 765.
+// token at a time and knows no cycles / now: CAG repeated to 20,000 bases 980 /
+// 4,210 / 101, to 10^6 12,900 / 209,000 / 1,980; 1,024 rows of 500 to 20,000
+// random bases with a repeat of 40 to 250 every 2,000 1,420 / 2,370 / 760.
 constexpr int kRing = 64;        // tokens remembered, to find a cycle of up to half of them
 constexpr int kCycle = 1024;     // bases of the longest cycle
 constexpr int kCycleEvery = 8;   // tokens between two looks for one

@@ -144,7 +144,7 @@ struct Workspace {
     uint64_t *d_status = nullptr;  // 2 * cap words (parity 0 then parity 1)
     int64_t cap = 0;               // tiles
     int64_t high_water = 0;        // tiles that may hold non-zero status
-    uint64_t *d_decode = nullptr;  // kDecodeWords words of the decode's scan over tiles, from the first decode
+    uint64_t *d_decode = nullptr;  // kDecodeWords words of the decode's scan over tiles, from the first decode or scratch
                                    // or the first scratch on
     uint8_t *d_scratch = nullptr;  // general scratch for multi-pass kernels (BPE)
     int64_t scratch_bytes = 0;
